@@ -289,6 +289,19 @@ __global__ __launch_bounds__(kSB) void k_stage(cplx<T>* __restrict__ psi, StageG
     tile_store(psi, tile, g, offhi, base);
 }
 
+// The adjoint needs Im Tr(A M) with Hermitian A only, so of M = sum_f psi_f
+// lam_f^dagger it keeps the anti-Hermitian part (M - M^dagger) / 2: D * D reals
+// per tile instead of 2 D * D.  Entry a * D + c of a tile's row holds its real
+// part (antisymmetric) for a < c, its imaginary part (symmetric) for a >= c.
+template <int D, class F>
+__device__ __forceinline__ double anti_entry(uint32_t e, F&& m) {
+    const uint32_t a = e / D, c = e % D;
+    double re0, im0, re1, im1;
+    m(a * D + c, re0, im0);
+    m(c * D + a, re1, im1);
+    return a < c ? 0.5 * (re0 - re1) : 0.5 * (im0 + im1);
+}
+
 // Reverse stage on psi and lam.  Before a U with slot >= 0, lane (entry, part)
 // sums psi_f[a] conj(lam_f[c]) over the fibres f = part, part + P, ... and the
 // parts are then added in a fixed order.
@@ -334,16 +347,15 @@ __global__ __launch_bounds__(kSB) void k_stage_adj(cplx<T>* __restrict__ psi, cp
                 red[0][threadIdx.x] = ar;
                 red[1][threadIdx.x] = ai;
                 __syncthreads();
-                if (int(threadIdx.x) < E) {
-                    double sr = 0.0, si = 0.0;
-                    for (int p = 0; p < P; ++p) {
-                        sr += red[0][p * E + threadIdx.x];
-                        si += red[1][p * E + threadIdx.x];
-                    }
-                    double* o = partial + ((size_t(op.slot) * nblocks + blk) * E + threadIdx.x) * 2;
-                    o[0] = sr;
-                    o[1] = si;
-                }
+                if (int(threadIdx.x) < E)
+                    partial[(size_t(op.slot) * nblocks + blk) * E + threadIdx.x] =
+                        anti_entry<D>(threadIdx.x, [&](uint32_t j, double& sr, double& si) {
+                            sr = si = 0.0;
+                            for (int p = 0; p < P; ++p) {
+                                sr += red[0][p * E + j];
+                                si += red[1][p * E + j];
+                            }
+                        });
                 __syncthreads();
             }
             op_u<T, D>(tp, g, op, mats + op.mat);
@@ -370,38 +382,59 @@ __global__ __launch_bounds__(kSB) void k_stage_adj(cplx<T>* __restrict__ psi, cp
     tile_store(lam, tl, g, offhi, base);
 }
 
-// One workgroup per (register, slot, entry): lanes sum the tiles
-// i = lane, lane + 256, ... of the register, then a fixed tree.
-__global__ __launch_bounds__(kSB) void k_stage_mreduce(const double* __restrict__ partial, uint32_t nslots,
-                                                       uint32_t ntiles, uint32_t batch, uint32_t E,
+// Sums the tiles' rows of E entries (anti_entry form) of every (register, slot)
+// in a fixed order.  HBM-bound: each workgroup owns a chunk of consecutive rows
+// and reads them whole (lane = entry of one of 256 / E rows at a time, eight
+// rows in flight per lane).  mout == nullptr: the chunk's sum replaces its first
+// row (no other workgroup reads the chunk); a second launch adds those rows
+// (every step-th) and writes the complex D x D matrix.  Reads 8 D^2 bytes a tile
+// once: 58 us for two slots of 10^5 tiles at D = 10 (2.9 TB/s; 365 us with one
+// workgroup per entry, which read 16 bytes of every row of complex entries),
+// 9.4 us for 15,625 tiles at D = 5 (27 us).
+__global__ __launch_bounds__(kSB) void k_stage_mreduce(double* __restrict__ partial, uint32_t nslots, uint32_t ntiles,
+                                                       uint32_t batch, uint32_t D, uint32_t chunk, uint32_t step,
                                                        double* __restrict__ mout, uint32_t nslots_total,
                                                        uint32_t slot0) {
-    __shared__ double red[2][kSB];
-    const uint32_t e = blockIdx.x % E;
-    const uint32_t bj = blockIdx.x / E;
-    const uint32_t b = bj / nslots;
-    const uint32_t j = bj - b * nslots;
-    const uint32_t nblocks = ntiles * batch;
-    double ar = 0.0, ai = 0.0;
-    for (uint32_t i = threadIdx.x; i < ntiles; i += kSB) {
-        const double* p = partial + ((size_t(j) * nblocks + b * ntiles + i) * E + e) * 2;
-        ar += p[0];
-        ai += p[1];
-    }
-    red[0][threadIdx.x] = ar;
-    red[1][threadIdx.x] = ai;
-    __syncthreads();
-    for (int w = kSB / 2; w > 0; w >>= 1) {
-        if (int(threadIdx.x) < w) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + w];
-            red[1][threadIdx.x] += red[1][threadIdx.x + w];
+    __shared__ double red[kSB];
+    __shared__ double sum[kSB];
+    const uint32_t E = D * D;
+    const uint32_t nch = (ntiles + chunk - 1) / chunk;
+    const uint32_t ch = blockIdx.x % nch, bj = blockIdx.x / nch;
+    const uint32_t b = bj / nslots, j = bj - b * nslots;
+    double* rows = partial + (size_t(j) * ntiles * batch + size_t(b) * ntiles) * E;
+    const uint32_t first = ch * chunk, last = min(ntiles, first + chunk);
+    const uint32_t G = kSB / E, gr = threadIdx.x / E, e = threadIdx.x - gr * E;
+    constexpr int kU = 8;
+    double acc = 0.0;
+    if (gr < G) {
+        const size_t gs = size_t(G) * step;
+        size_t i = first + size_t(gr) * step;
+        for (; i + (kU - 1) * gs < last; i += kU * gs) {
+            double x[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) x[u] = rows[(i + u * gs) * E + e];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) acc += x[u];
         }
-        __syncthreads();
+        for (; i < last; i += gs) acc += rows[i * E + e];
     }
-    if (threadIdx.x == 0) {
-        double* o = mout + ((size_t(b) * nslots_total + slot0 + j) * E + e) * 2;
-        o[0] = red[0][0];
-        o[1] = red[1][0];
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x < E) {
+        double t = 0.0;
+        for (uint32_t q = 0; q < G; ++q) t += red[q * E + threadIdx.x];
+        if (mout == nullptr)
+            rows[size_t(first) * E + threadIdx.x] = t;
+        else
+            sum[threadIdx.x] = t;
+    }
+    if (mout == nullptr) return;
+    __syncthreads();
+    if (threadIdx.x < E) {
+        const uint32_t r = threadIdx.x / D, c = threadIdx.x - r * D;
+        double* o = mout + ((size_t(b) * nslots_total + slot0 + j) * E + threadIdx.x) * 2;
+        o[0] = r == c ? 0.0 : r < c ? sum[r * D + c] : -sum[c * D + r];
+        o[1] = r < c ? sum[c * D + r] : sum[r * D + c];
     }
 }
 
@@ -846,15 +879,14 @@ __device__ __forceinline__ void mreduce_block(MAcc<T, D>& m, double (*red)[kSB],
         }
     }
     __syncthreads();
-    if (threadIdx.x < uint32_t(E)) {
-        double sr = 0.0, si = 0.0;
-        for (uint32_t q = 0; q < nrows; ++q) {
-            sr += red[0][q * E + threadIdx.x];
-            si += red[1][q * E + threadIdx.x];
-        }
-        out[2 * threadIdx.x] = sr;
-        out[2 * threadIdx.x + 1] = si;
-    }
+    if (threadIdx.x < uint32_t(E))
+        out[threadIdx.x] = anti_entry<D>(threadIdx.x, [&](uint32_t j, double& sr, double& si) {
+            sr = si = 0.0;
+            for (uint32_t q = 0; q < nrows; ++q) {
+                sr += red[0][q * E + j];
+                si += red[1][q * E + j];
+            }
+        });
     __syncthreads();
 }
 
@@ -990,7 +1022,7 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
     }
     if constexpr (MACC) {
         if (ma.mslot >= 0)
-            mreduce_block<T, D>(macc, ma.red, ma.partial + (size_t(ma.mslot) * gridDim.x + ma.blk) * (D * D) * 2);
+            mreduce_block<T, D>(macc, ma.red, ma.partial + (size_t(ma.mslot) * gridDim.x + ma.blk) * (D * D));
     }
 }
 
@@ -1133,7 +1165,7 @@ __device__ inline void tile_m(const cplx<T>* tp, const cplx<T>* tl, const StageG
     constexpr uint32_t NBR = D / B, NB = NBR * NBR;
     const uint32_t nt = blockDim.x;
     const uint32_t nf = g.TE / D;
-    double* out = partial + (size_t(op.slot) * gridDim.x + blk) * E * 2;
+    double* out = partial + (size_t(op.slot) * gridDim.x + blk) * E;
     auto block_sum = [&](uint32_t bi, uint32_t f0, uint32_t step, T (&ar)[B * B], T (&ai)[B * B]) {
         const uint32_t a0 = (bi / NBR) * B, c0 = (bi % NBR) * B;
 #pragma unroll
@@ -1172,21 +1204,23 @@ __device__ inline void tile_m(const cplx<T>* tp, const cplx<T>* tl, const StageG
             }
             __syncthreads();
         }
-        for (uint32_t e = threadIdx.x; e < E; e += nt) {
-            out[2 * e] = red[0][e];
-            out[2 * e + 1] = red[1][e];
-        }
     } else {
         for (uint32_t bi = threadIdx.x; bi < NB; bi += nt) {
             T ar[B * B], ai[B * B];
             block_sum(bi, 0, 1, ar, ai);
 #pragma unroll
             for (int j = 0; j < B * B; ++j) {
-                out[2 * entry(bi, j)] = double(ar[j]);
-                out[2 * entry(bi, j) + 1] = double(ai[j]);
+                red[0][entry(bi, j)] = double(ar[j]);
+                red[1][entry(bi, j)] = double(ai[j]);
             }
         }
+        __syncthreads();
     }
+    for (uint32_t e = threadIdx.x; e < E; e += nt)
+        out[e] = anti_entry<D>(e, [&](uint32_t j, double& sr, double& si) {
+            sr = red[0][j];
+            si = red[1][j];
+        });
     __syncthreads();
 }
 
@@ -1463,11 +1497,20 @@ qf_status launch_stage_adj(const StateView& s, void* lam, const StageGeom& g, co
     });
 }
 
-qf_status launch_stage_mreduce(const double* partial, uint32_t nslots, uint32_t ntiles, uint32_t batch, uint32_t E,
+// Rows of a chunk: up to 1024 rows are added in one launch; more in two, of about
+// the square root each, so that both levels have many short workgroups.
+qf_status launch_stage_mreduce(double* partial, uint32_t nslots, uint32_t ntiles, uint32_t batch, uint32_t D,
                                double* mout, uint32_t nslots_total, uint32_t slot0, hipStream_t st) {
     if (nslots == 0) return QF_OK;
-    hipLaunchKernelGGL(k_stage_mreduce, dim3(batch * nslots * E), dim3(kSB), 0, st, partial, nslots, ntiles, batch,
-                       E, mout, nslots_total, slot0);
+    uint32_t step = 1;
+    if (ntiles > 1024) {
+        while (uint64_t(step) * step < ntiles) ++step;
+        hipLaunchKernelGGL(k_stage_mreduce, dim3(batch * nslots * ((ntiles + step - 1) / step)), dim3(kSB), 0, st,
+                           partial, nslots, ntiles, batch, D, step, 1u, nullptr, nslots_total, slot0);
+        QF_CHECK(check_launch("stage M reduce (chunks)"));
+    }
+    hipLaunchKernelGGL(k_stage_mreduce, dim3(batch * nslots), dim3(kSB), 0, st, partial, nslots, ntiles, batch, D,
+                       ntiles, step, mout, nslots_total, slot0);
     return check_launch("stage M reduce");
 }
 

@@ -1982,7 +1982,7 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
     size_t pdoubles = 1;
     if (stg) {
         for (const Pass& ps : plan->rev.passes)
-            if (ps.tile) pdoubles = std::max(pdoubles, size_t(ps.nslots) * ps.geom.ntiles * v.batch * E * 2);
+            if (ps.tile) pdoubles = std::max(pdoubles, size_t(ps.nslots) * ps.geom.ntiles * v.batch * E);
     } else {
         pdoubles = std::max<size_t>(adj_axis_partial_doubles(v), 1);
     }
@@ -2017,7 +2017,7 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
             if (ps.tile) {
                 rs = run_tile_pass(plan, plan->rev, ps, v, lam->amps, partial, st);
                 if (rs == QF_OK)
-                    rs = launch_stage_mreduce(partial, ps.nslots, ps.geom.ntiles, v.batch, uint32_t(E), mdev,
+                    rs = launch_stage_mreduce(partial, ps.nslots, ps.geom.ntiles, v.batch, uint32_t(D), mdev,
                                               uint32_t(plan->rev.nslots), uint32_t(ps.slot0), st);
             } else if (ps.cr_slot >= 0) {
                 const size_t esz = plan->dtype == QF_C64 ? 8 : 16;
@@ -2615,7 +2615,7 @@ qf_status qf_plan_bind(qf_plan* plan, int64_t batch) {
     step(dev_alloc(&plan->rev.dmats_b, std::max<size_t>(plan->rev.nmats, 1) * esz * size_t(batch)));
     size_t pd = 1;
     for (const Pass& ps : plan->rev.passes)
-        if (ps.tile) pd = std::max(pd, size_t(ps.nslots) * ps.geom.ntiles * size_t(batch) * E * 2);
+        if (ps.tile) pd = std::max(pd, size_t(ps.nslots) * ps.geom.ntiles * size_t(batch) * E);
     if (plan->rev.ncr > 0) pd = std::max(pd, crot_partial_doubles(uniform_view(D, plan->n, batch, plan->dtype)));
     step(dev_alloc(reinterpret_cast<void**>(&plan->w_partial), pd * sizeof(double)));
     step(dev_alloc(reinterpret_cast<void**>(&plan->w_m),
@@ -2715,7 +2715,7 @@ qf_status qf_adjoint_grad_dev(qf_plan* plan, const qf_state* psi, const qf_state
             else
                 QF_CHECK(launch_stage_adj(v, lam->amps, ps.geom, L.dops + ps.op_off, ps.nops, mats, plan->w_partial,
                                           st, L.nmats));
-            QF_CHECK(launch_stage_mreduce(plan->w_partial, ps.nslots, ps.geom.ntiles, v.batch, uint32_t(E), plan->w_m,
+            QF_CHECK(launch_stage_mreduce(plan->w_partial, ps.nslots, ps.geom.ntiles, v.batch, uint32_t(D), plan->w_m,
                                           uint32_t(L.nslots), uint32_t(ps.slot0), st));
         } else if (ps.cr_slot >= 0) {
             const void* tab = reinterpret_cast<const unsigned char*>(L.dmats_b) + ps.mat_off * esz;

@@ -239,8 +239,8 @@ int max_group_size(uint32_t D);
 qf_status launch_stage_rounds(const StateView& s, int M, const StageGeom& g, const RoundDesc* drounds, int nrounds,
                               const StageOp* dops, const void* dmats, hipStream_t st, size_t mat_stride = 0);
 // Reverse stage: applies the (already inverted) ops to psi and lam; before each
-// U with slot >= 0 it accumulates M = sum_f psi_f lam_f^dagger over the tile
-// into partial[(slot * nblocks + block) * D*D] (complex FP64).
+// U with slot >= 0 it sums M = sum_f psi_f lam_f^dagger over the tile and writes
+// its anti-Hermitian part (D*D FP64 values) to partial[(slot * nblocks + block) * D*D].
 qf_status launch_stage_adj(const StateView& s, void* lam, const StageGeom& g, const StageOp* dops, int nops,
                            const void* dmats, double* partial, hipStream_t st, size_t mat_stride = 0);
 // Pipelined persistent forward stage (register rounds, M <= 3, D <= 12, complex64): grid of at most
@@ -254,9 +254,10 @@ qf_status launch_stage_pipe(const StateView& s, int M, const StageGeom& g, const
 qf_status launch_stage_adj_rounds(const StateView& s, void* lam, int M, const StageGeom& g, const RoundDesc* drounds,
                                   int nrounds, const StageOp* dops, const void* dmats, double* partial, hipStream_t st,
                                   size_t mat_stride = 0);
-// mout[(b * nslots_total + slot0 + j) * E] = sum over the tiles of register b of
-// partial[j], for j < nslots (fixed order).
-qf_status launch_stage_mreduce(const double* partial, uint32_t nslots, uint32_t ntiles, uint32_t batch, uint32_t E,
+// mout[(b * nslots_total + slot0 + j) * D*D] = sum over the tiles of register b of
+// partial[j], for j < nslots (fixed order), as a complex D x D matrix (the
+// anti-Hermitian part of M).  Overwrites partial.
+qf_status launch_stage_mreduce(double* partial, uint32_t nslots, uint32_t ntiles, uint32_t batch, uint32_t D,
                                double* mout, uint32_t nslots_total, uint32_t slot0, hipStream_t st);
 size_t stage_lds_bytes(const StageGeom& g, int dtype, bool adjoint);
 
