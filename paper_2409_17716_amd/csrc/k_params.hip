@@ -106,6 +106,12 @@ __global__ void k_build_mats(const DevGroup* __restrict__ groups, int ngroups, c
         DMat<D> a;
         dm_identity<D>(a);
         for (int i = 0; i < gr.ng; ++i) dm_apply_gate<D>(gates[gr.g0 + i], th, gr.inv != 0, a);
+        if (gr.real) {
+            T* o = reinterpret_cast<T*>(out);
+            for (int r = 0; r < D; ++r)
+                for (int c = 0; c < D; ++c) o[r * D + c] = T(a.m[r][c].re);
+            return;
+        }
         for (int r = 0; r < D; ++r)
             for (int c = 0; c < D; ++c) out[r * D + c] = cmake<T>(T(a.m[r][c].re), T(a.m[r][c].im));
     } else if (gr.type == DG_CR) {

@@ -171,7 +171,7 @@ __device__ inline void matvec(const cplx<T>* __restrict__ M, bool real, const cp
             T re = 0, im = 0;
 #pragma unroll
             for (int b = 0; b < D; ++b) {
-                const T m = M[a * D + b].re;
+                const T m = reinterpret_cast<const T*>(M)[a * D + b];
                 re = fma(m, v[b].re, re);
                 im = fma(m, v[b].im, im);
             }
@@ -459,7 +459,9 @@ __device__ constexpr int rdigit(int i) {
 
 // U on group position J: every fibre along J (digits of the other positions
 // fixed) is multiplied by U.  The matrix is uniform and held in scalar
-// registers; REAL uses only its real parts.
+// registers; a REAL one is stored as D * D reals (wide scalar loads: a 10 x 10
+// matrix takes 7 instead of the 100 that its real parts took inside a complex
+// one).
 template <typename T, int D, int M, int J, bool REAL>
 __device__ __forceinline__ void r_u(cplx<T> (&v)[cpow(D, M)], const cplx<T>* __restrict__ U) {
     constexpr int SJ = cpow(D, M - 1 - J);
@@ -468,14 +470,16 @@ __device__ __forceinline__ void r_u(cplx<T> (&v)[cpow(D, M)], const cplx<T>* __r
     // are read from memory where used (a local copy spills into vector
     // registers and lowers occupancy)
     constexpr bool kCopy = D <= 4;
-    cplx<T> m[kCopy ? D * D : 1];
+    using Elem = std::conditional_t<REAL, T, cplx<T>>;
+    const Elem* __restrict__ Um = reinterpret_cast<const Elem*>(U);
+    Elem m[kCopy ? D * D : 1];
     if constexpr (kCopy) {
 #pragma unroll
-        for (int e = 0; e < D * D; ++e) m[e] = U[e];
+        for (int e = 0; e < D * D; ++e) m[e] = Um[e];
     }
-    auto mat = [&](int e) -> cplx<T> {
+    auto mat = [&](int e) -> Elem {
         if constexpr (kCopy) return m[e];
-        else return U[e];
+        else return Um[e];
     };
 #pragma unroll
     for (int c = 0; c < NF; ++c) {
@@ -487,7 +491,7 @@ __device__ __forceinline__ void r_u(cplx<T> (&v)[cpow(D, M)], const cplx<T>* __r
                 T re = 0, im = 0;
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    const T w = mat(a * D + d).re;
+                    const T w = mat(a * D + d);
                     re = fma(w, v[b0 + d * SJ].re, re);
                     im = fma(w, v[b0 + d * SJ].im, im);
                 }

@@ -1464,6 +1464,17 @@ static void put_mat(void* base, size_t off, const Mat& m) {
     for (size_t i = 0; i < m.size(); ++i) d[i] = cmake<T>(T(m[i].real()), T(m[i].imag()));
 }
 
+// The real parts as consecutive reals (a real U), from complex element off on.
+static void put_real(int dtype, void* base, size_t off, const Mat& m) {
+    if (dtype == QF_C64) {
+        float* d = reinterpret_cast<float*>(base) + 2 * off;
+        for (size_t i = 0; i < m.size(); ++i) d[i] = float(m[i].real());
+    } else {
+        double* d = reinterpret_cast<double*>(base) + 2 * off;
+        for (size_t i = 0; i < m.size(); ++i) d[i] = m[i].real();
+    }
+}
+
 // Build every stage matrix from theta into the pinned staging buffer and copy it
 // to the device on `st`.
 static qf_status upload_mats(const qf_plan* p, PassList& L, const double* theta, hipStream_t st) {
@@ -1506,7 +1517,9 @@ static qf_status upload_mats(const qf_plan* p, PassList& L, const double* theta,
             const StageOp& so = L.hops[ps.op_off + i];
             if (h.type == SOP_U) {
                 const Mat U = group_matrix(p, h.g, theta);
-                if (p->dtype == QF_C64)
+                if (so.real)
+                    put_real(p->dtype, L.hmats, ps.mat_off + so.mat, U);
+                else if (p->dtype == QF_C64)
                     put_mat<float>(L.hmats, ps.mat_off + so.mat, U);
                 else
                     put_mat<double>(L.hmats, ps.mat_off + so.mat, U);
@@ -2511,7 +2524,7 @@ static void bound_groups(qf_plan* p, PassList& L) {
     for (const Pass& ps : L.passes) {
         if (!ps.tile && ps.cr_slot >= 0) {
             L.hgroups.push_back(DevGroup{DG_CR, uint32_t(ps.mat_off), int32_t(p->hgates.size()), 1,
-                                         ps.fused.inv ? 1 : 0});
+                                         ps.fused.inv ? 1 : 0, 0});
             p->hgates.push_back(dev_gate(p->gates[ps.fused.gi].op));
         }
         if (!ps.tile) continue;
@@ -2520,14 +2533,16 @@ static void bound_groups(qf_plan* p, PassList& L) {
             const StageOp& so = L.hops[ps.op_off + i];
             if (h.type == SOP_U) {
                 DevGroup g{DG_U, uint32_t(ps.mat_off + so.mat), int32_t(p->hgates.size()), int32_t(h.g.size()),
-                           h.g[0].inv ? 1 : 0};
+                           h.g[0].inv ? 1 : 0, so.real};
                 for (const GRef& r : h.g) p->hgates.push_back(dev_gate(op_of(p, r)));
                 L.hgroups.push_back(g);
             } else if (h.type == SOP_PHASE) {
                 for (size_t j = 0; j < h.g.size(); ++j)
-                    L.hgroups.push_back(DevGroup{DG_CZ, uint32_t(ps.mat_off + so.ptab[j]), 0, 0, h.g[j].inv ? 1 : 0});
+                    L.hgroups.push_back(
+                        DevGroup{DG_CZ, uint32_t(ps.mat_off + so.ptab[j]), 0, 0, h.g[j].inv ? 1 : 0, 0});
                 if (ps.nrounds > 0)
-                    L.hgroups.push_back(DevGroup{DG_W, uint32_t(ps.mat_off + so.wtab), 0, 0, h.g[0].inv ? 1 : 0});
+                    L.hgroups.push_back(
+                        DevGroup{DG_W, uint32_t(ps.mat_off + so.wtab), 0, 0, h.g[0].inv ? 1 : 0, 0});
             }
         }
     }

@@ -218,7 +218,7 @@ struct StageOp {
     int32_t shifts[16];   // SHIFT: x_t -> x_t + shifts[x_c] (already in [0, D))
     int32_t shift_mul;    // SHIFT: shifts[c] = (shift_mul * c + shifts[0]) mod D, or -1 if not affine
     int32_t mat;          // U: offset (complex elements) of the D x D matrix
-    int32_t real;         // U: all imaginary parts are zero
+    int32_t real;         // U: all imaginary parts are zero; the matrix is stored as D * D reals
     int32_t slot;         // adjoint: M slot of this U inside the stage, -1 = none
     int32_t npairs;       // PHASE: number of two-qudit diagonal factors
     FastDiv pa[kMaxPairs], pb[kMaxPairs];  // PHASE: global strides of the two qudits
@@ -277,6 +277,7 @@ struct DevGroup {
     uint32_t mat_off;  // complex elements from the start of a register's matrices
     int32_t g0, ng;    // DG_U: gates [g0, g0 + ng) of the gate list, application order; DG_CR: gate g0
     int32_t inv;       // DG_U: every gate is applied as its inverse; DG_CZ / DG_W: conjugated
+    int32_t real;      // DG_U: stored as D * D reals
 };
 // A fused run that owns an adjoint M slot; its gates in forward order.
 struct DevGradGroup {
