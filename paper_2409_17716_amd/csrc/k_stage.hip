@@ -29,6 +29,8 @@ namespace {
 
 constexpr int kSB = 256;
 
+constexpr int cpow(int b, int e) { return e == 0 ? 1 : b * cpow(b, e - 1); }
+
 // Workgroup barrier for LDS data only: waits for this wave's LDS operations
 // (lgkmcnt) and meets the other waves, without the fence of __syncthreads that
 // would also wait for every outstanding global load (the pipelined kernel keeps
@@ -161,6 +163,89 @@ template <typename T>
 __device__ inline void tile_store(cplx<T>* __restrict__ psi, const cplx<T>* tile, const StageGeom& g,
                                   const uint32_t* offhi, uint32_t base) {
     tile_io<T, false>(psi, const_cast<cplx<T>*>(tile), g, offhi, base);
+}
+
+// Round kernels take their geometry from the pass's table (stage_table): the
+// tile's base and every lane's digits are loads instead of chains of divisions
+// and scalar loads, 2,000 cycles and more before a workgroup's first tile load.
+__device__ __forceinline__ uint32_t table_base(const StageGeom& g, const uint32_t* __restrict__ tab, uint32_t blk) {
+    const uint32_t b = g.div_ntiles.div(blk), t = blk - b * g.ntiles;
+    const uint32_t hi = g.div_out.div(t), lo = t - hi * g.div_out.d;
+    return b * g.N + tab[g.t_outhi + hi] + tab[g.t_outlo + lo];
+}
+
+__device__ __forceinline__ void table_offhi(const StageGeom& g, const uint32_t* __restrict__ tab, uint32_t* offhi) {
+    for (uint32_t h = threadIdx.x; h < g.nhi; h += blockDim.x) offhi[h] = tab[g.t_offhi + h];
+}
+
+// Tile I/O by digits: lane l < A = D^a takes the tile elements l + A j.  Its a low
+// digits are fixed, so its HBM offset is one table entry and step j adds a uniform
+// one: a global access needs no vector instruction for its address (scalar base
+// plus lane offset) and an LDS access one add, against seven or eight per element
+// for the runs above.  B steps of every tile are in flight.
+template <typename T, int B, bool LOAD, int NT, typename At>
+__device__ __forceinline__ void io_steps(cplx<T>* const (&psi)[NT], cplx<T>* const (&tile)[NT], const StageGeom& g,
+                                         const uint32_t* __restrict__ tab, At&& at) {
+    const uint32_t* __restrict__ steps = tab + g.t_steps;
+    uint32_t e = threadIdx.x;
+    for (uint32_t j = 0; j < g.nstep; j += B) {
+        cplx<T> v[NT][B];
+        if (LOAD) {
+#pragma unroll
+            for (int x = 0; x < NT; ++x)
+#pragma unroll
+                for (int c = 0; c < B; ++c) v[x][c] = at(psi[x] + steps[j + c]);
+#pragma unroll
+            for (int x = 0; x < NT; ++x)
+#pragma unroll
+                for (int c = 0; c < B; ++c) tile[x][e + c * g.io_lanes] = v[x][c];
+        } else {
+#pragma unroll
+            for (int x = 0; x < NT; ++x)
+#pragma unroll
+                for (int c = 0; c < B; ++c) v[x][c] = tile[x][e + c * g.io_lanes];
+#pragma unroll
+            for (int x = 0; x < NT; ++x)
+#pragma unroll
+                for (int c = 0; c < B; ++c) at(psi[x] + steps[j + c]) = v[x][c];
+        }
+        e += B * g.io_lanes;
+    }
+}
+
+// The NT tiles' elements from (LOAD) or to the states at psi.  Steps in flight: a
+// power of D (so that it divides the step count), 8 to 25, at most 64 registers;
+// D = 3 with 3 instead of 9: 7.0 against 5.8 ms per forward of 3^16.
+template <typename T, int D, int M, bool LOAD, int NT>
+__device__ __forceinline__ void tiles_io(cplx<T>* const (&psi)[NT], cplx<T>* const (&tile)[NT], const StageGeom& g,
+                                         const uint32_t* __restrict__ tab, const uint32_t* offhi, uint32_t base,
+                                         uint32_t lane_off) {
+    if (g.io_lanes == 0) {
+#pragma unroll
+        for (int x = 0; x < NT; ++x) tile_io<T, LOAD>(psi[x], tile[x], g, offhi, base);
+        return;
+    }
+    if (threadIdx.x >= g.io_lanes) return;
+    cplx<T>* pb[NT];
+#pragma unroll
+    for (int x = 0; x < NT; ++x) pb[x] = psi[x] + base;
+    constexpr int kPow = D == 2 ? 8 : D == 3 ? 9 : D == 4 ? 16 : D == 5 && M == 2 ? 25 : D;
+    constexpr int kBig = NT * kPow * int(sizeof(T) / 2) <= 64 ? kPow : D;
+    auto run = [&](auto&& at) {
+        if (g.nstep % kBig == 0)
+            io_steps<T, kBig, LOAD, NT>(pb, tile, g, tab, at);
+        else if (kBig != D && g.nstep % D == 0)
+            io_steps<T, D, LOAD, NT>(pb, tile, g, tab, at);
+        else
+            io_steps<T, 1, LOAD, NT>(pb, tile, g, tab, at);
+    };
+    if (uint64_t(g.N) * sizeof(cplx<T>) <= 0xffffffffull) {
+        // registers below 4 GB: scalar base and 32-bit lane offset
+        const uint32_t lb = lane_off * uint32_t(sizeof(cplx<T>));
+        run([&](cplx<T>* p) -> cplx<T>& { return *reinterpret_cast<cplx<T>*>(reinterpret_cast<char*>(p) + lb); });
+    } else {
+        run([&](cplx<T>* p) -> cplx<T>& { return p[lane_off]; });
+    }
 }
 
 template <typename T, int D>
@@ -449,8 +534,6 @@ __global__ __launch_bounds__(kSB) void k_stage_mreduce(double* __restrict__ part
 // are folded into the LDS addresses of the loads (before the in-place ops) or
 // of the stores (after them) and cost no register moves (load_addrs).
 // ---------------------------------------------------------------------------
-
-constexpr int cpow(int b, int e) { return e == 0 ? 1 : b * cpow(b, e - 1); }
 
 template <int D, int M, int J>
 __device__ constexpr int rdigit(int i) {
@@ -1034,32 +1117,39 @@ template <typename T, int D, int M>
 __device__ __forceinline__ void stage_rounds(cplx<T>* __restrict__ psi, const StageGeom& g,
                                              const RoundDesc* __restrict__ rounds, int nrounds,
                                              const StageOp* __restrict__ ops, const cplx<T>* __restrict__ mats,
-                                             size_t mat_stride) {
+                                             size_t mat_stride, const uint32_t* __restrict__ tab) {
     const uint32_t blk = tile_of_block(g);
-    mats += size_t(blk / g.ntiles) * mat_stride;
+    mats += size_t(g.div_ntiles.div(blk)) * mat_stride;
     extern __shared__ unsigned char smem[];
     cplx<T>* tile = reinterpret_cast<cplx<T>*>(smem);
     uint32_t* offhi = reinterpret_cast<uint32_t*>(tile + g.TE);
-    const uint32_t base = tile_base<D>(g, blk);
-    build_offhi<D>(g, offhi);
-    __syncthreads();
-    tile_load(psi, tile, g, offhi, base);
-    __syncthreads();
-    const SubDigits dig0 = sub_digits<D>(threadIdx.x, nrounds > 0 ? rounds[0].nother : 0);
+    const uint4 lane = reinterpret_cast<const uint4*>(tab)[threadIdx.x];
+    const uint32_t base = table_base(g, tab, blk);
+    if (g.use_offhi) {
+        table_offhi(g, tab, offhi);
+        if (g.io_lanes == 0) __syncthreads();
+    }
+    cplx<T>* const st[1] = {psi};
     cplx<T>* const tl[1] = {tile};
+    tiles_io<T, D, M, true, 1>(st, tl, g, tab, offhi, base, lane.x);
+    __syncthreads();
+    SubDigits dig0;
+    dig0.w[0] = lane.y;
+    dig0.w[1] = lane.z;
     for (int ri = 0; ri < nrounds; ++ri) {
         run_round<T, D, M, 1>(tl, g, offhi, base, rounds[ri], ops, mats, dig0);
         __syncthreads();
     }
-    tile_store(psi, tile, g, offhi, base);
+    tiles_io<T, D, M, false, 1>(st, tl, g, tab, offhi, base, lane.x);
 }
 
 template <typename T, int D, int M>
 __global__ __launch_bounds__(kSB) void k_stage_rounds(cplx<T>* __restrict__ psi, StageGeom g,
                                                       const RoundDesc* __restrict__ rounds, int nrounds,
                                                       const StageOp* __restrict__ ops,
-                                                      const cplx<T>* __restrict__ mats, size_t mat_stride) {
-    stage_rounds<T, D, M>(psi, g, rounds, nrounds, ops, mats, mat_stride);
+                                                      const cplx<T>* __restrict__ mats, size_t mat_stride,
+                                                      const uint32_t* __restrict__ tab) {
+    stage_rounds<T, D, M>(psi, g, rounds, nrounds, ops, mats, mat_stride, tab);
 }
 
 // The same kernel compiled for 8 waves per SIMD.  The default build of these
@@ -1070,8 +1160,9 @@ __global__ __launch_bounds__(kSB) void k_stage_rounds(cplx<T>* __restrict__ psi,
 template <typename T, int D, int M>
 __global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(8))) void k_stage_rounds_w8(
     cplx<T>* __restrict__ psi, StageGeom g, const RoundDesc* __restrict__ rounds, int nrounds,
-    const StageOp* __restrict__ ops, const cplx<T>* __restrict__ mats, size_t mat_stride) {
-    stage_rounds<T, D, M>(psi, g, rounds, nrounds, ops, mats, mat_stride);
+    const StageOp* __restrict__ ops, const cplx<T>* __restrict__ mats, size_t mat_stride,
+    const uint32_t* __restrict__ tab) {
+    stage_rounds<T, D, M>(psi, g, rounds, nrounds, ops, mats, mat_stride, tab);
 }
 
 // Instantiations that take k_stage_rounds_w8: default occupancy below 8 and
@@ -1236,22 +1327,28 @@ __global__ __launch_bounds__(kSB) void k_stage_adj_rounds(cplx<T>* __restrict__ 
                                                           StageGeom g, const RoundDesc* __restrict__ rounds,
                                                           int nrounds, const StageOp* __restrict__ ops,
                                                           const cplx<T>* __restrict__ mats, size_t mat_stride,
-                                                          double* __restrict__ partial) {
+                                                          double* __restrict__ partial,
+                                                          const uint32_t* __restrict__ tab) {
     const uint32_t blk = tile_of_block(g);
-    mats += size_t(blk / g.ntiles) * mat_stride;
+    mats += size_t(g.div_ntiles.div(blk)) * mat_stride;
     extern __shared__ unsigned char smem[];
     cplx<T>* tp = reinterpret_cast<cplx<T>*>(smem);
     cplx<T>* tl = tp + g.TE;
     uint32_t* offhi = reinterpret_cast<uint32_t*>(tl + g.TE);
     __shared__ double red[2][kSB];
-    const uint32_t base = tile_base<D>(g, blk);
-    build_offhi<D>(g, offhi);
-    __syncthreads();
-    tile_load(psi, tp, g, offhi, base);
-    tile_load(lam, tl, g, offhi, base);
-    __syncthreads();
-    const SubDigits dig0 = sub_digits<D>(threadIdx.x, nrounds > 0 ? rounds[0].nother : 0);
+    const uint4 lane = reinterpret_cast<const uint4*>(tab)[threadIdx.x];
+    const uint32_t base = table_base(g, tab, blk);
+    if (g.use_offhi) {
+        table_offhi(g, tab, offhi);
+        if (g.io_lanes == 0) __syncthreads();
+    }
+    cplx<T>* const st[2] = {psi, lam};
     cplx<T>* const tt[2] = {tp, tl};
+    tiles_io<T, D, M, true, 2>(st, tt, g, tab, offhi, base, lane.x);
+    __syncthreads();
+    SubDigits dig0;
+    dig0.w[0] = lane.y;
+    dig0.w[1] = lane.z;
     for (int ri = 0; ri < nrounds; ++ri) {
         const RoundDesc& rd = rounds[ri];
         // a slotted U opens its round (never after a leading permutation)
@@ -1270,8 +1367,7 @@ __global__ __launch_bounds__(kSB) void k_stage_adj_rounds(cplx<T>* __restrict__ 
         }
         __syncthreads();
     }
-    tile_store(psi, tp, g, offhi, base);
-    tile_store(lam, tl, g, offhi, base);
+    tiles_io<T, D, M, false, 2>(st, tt, g, tab, offhi, base, lane.x);
 }
 
 template <class F>
@@ -1328,10 +1424,62 @@ int max_group_size(uint32_t D) { return D == 2 ? 5 : D == 3 ? 3 : D <= 5 ? 2 : 1
 // Workgroup size of a register-round stage: the sub-tile count rounded up to
 // whole wavefronts, at most 256 (small sub-tile counts then leave no lanes idle
 // in the rounds and allow more resident workgroups).
-static uint32_t rounds_threads(const StageGeom& g, int DM) {
-    const uint32_t nsub = g.TE / uint32_t(DM);
+static uint32_t rounds_threads(const StageGeom& g, uint32_t DM) {
+    const uint32_t nsub = g.TE / DM;
     uint32_t t = (nsub + 63) / 64 * 64;
     return t < 64 ? 64 : t > uint32_t(kSB) ? uint32_t(kSB) : t;
+}
+
+// Geometry table of a round pass (32-bit words), appended to out:
+//   256 lanes x 4   HBM offset of tile element l (l mod TE); the digits of sub-tile
+//                   l over the k - M other tile qudits, one byte each, least
+//                   significant first (sub_digits); unused
+//   nstep           HBM offset of each step of io_lanes elements
+//   outlo, outhi    tile base by the low and high half of the outer digits
+//   nhi             run offsets (as in LDS)
+// io_lanes is the largest power of D within the workgroup and the tile; 0 where
+// it is half of the workgroup or less (D = 7, 8, 9 with 256 lanes): the tile then
+// moves by runs, which keep more lanes busy.
+void stage_table(uint32_t D, int M, StageGeom& g, std::vector<uint32_t>& out) {
+    out.clear();
+    std::vector<uint32_t> ts(g.k);  // global strides of the tile qudits, least significant first
+    for (uint32_t i = 0; i < g.k; ++i) ts[i] = i < g.r ? ipow(D, i) : g.hi_stride[g.k - 1 - i];
+    auto offset = [&](uint32_t u, uint32_t first) {
+        uint32_t off = 0;
+        for (uint32_t i = first; i < g.k; ++i, u /= D) off += u % D * ts[i];
+        return off;
+    };
+    const uint32_t nthr = rounds_threads(g, ipow(D, uint32_t(M)));
+    uint32_t a = 0, A = 1;
+    while (a < g.k && A * D <= nthr) {
+        A *= D;
+        ++a;
+    }
+    g.io_lanes = (2 * A > nthr || a == g.k) ? A : 0;
+    g.nstep = g.TE / A;
+    for (uint32_t l = 0; l < uint32_t(kSB); ++l) {
+        uint32_t w[2] = {0, 0};
+        uint32_t u = l;
+        for (uint32_t j = 0; j < 8 && j < g.k - uint32_t(M); ++j, u /= D) w[j >> 2] |= (u % D) << (8 * (j & 3));
+        out.insert(out.end(), {offset(l % g.TE, 0), w[0], w[1], 0u});
+    }
+    g.t_steps = uint32_t(out.size());
+    for (uint32_t j = 0; j < g.nstep; ++j) out.push_back(offset(j, a));
+    const uint32_t nlo = g.nout / 2;  // outer digits of the low half, least significant first
+    auto outer = [&](uint32_t u, uint32_t first, uint32_t count) {
+        uint32_t off = 0;
+        for (uint32_t i = 0; i < count; ++i, u /= D) off += u % D * g.out_stride[g.nout - 1 - first - i];
+        return off;
+    };
+    g.div_out.init(ipow(D, nlo));
+    g.t_outlo = uint32_t(out.size());
+    for (uint32_t i = 0; i < ipow(D, nlo); ++i) out.push_back(outer(i, 0, nlo));
+    g.t_outhi = uint32_t(out.size());
+    for (uint32_t i = 0; i < ipow(D, g.nout - nlo); ++i) out.push_back(outer(i, nlo, g.nout - nlo));
+    g.t_offhi = uint32_t(out.size());
+    for (uint32_t h = 0; h < g.nhi; ++h) out.push_back(offset(h, g.r));
+    while (out.size() % 4) out.push_back(0);
+    g.div_ntiles.init(g.ntiles);
 }
 
 template <typename T, int D, int M>
@@ -1343,11 +1491,11 @@ static qf_status launch_rounds_m(const StateView& s, const StageGeom& g, const R
     if constexpr (rounds_w8<T, D, M>())
         hipLaunchKernelGGL((k_stage_rounds_w8<T, D, M>), dim3(grid), dim3(nthr), lds, st,
                            reinterpret_cast<cplx<T>*>(s.amps), g, drounds, nrounds, dops,
-                           reinterpret_cast<const cplx<T>*>(dmats), mat_stride);
+                           reinterpret_cast<const cplx<T>*>(dmats), mat_stride, g.tab);
     else
         hipLaunchKernelGGL((k_stage_rounds<T, D, M>), dim3(grid), dim3(nthr), lds, st,
                            reinterpret_cast<cplx<T>*>(s.amps), g, drounds, nrounds, dops,
-                           reinterpret_cast<const cplx<T>*>(dmats), mat_stride);
+                           reinterpret_cast<const cplx<T>*>(dmats), mat_stride, g.tab);
     return check_launch("stage rounds");
 }
 
@@ -1456,7 +1604,7 @@ static qf_status launch_adj_rounds_m(const StateView& s, void* lam, const StageG
     const uint32_t nthr = rounds_threads(g, cpow(D, M));
     hipLaunchKernelGGL((k_stage_adj_rounds<T, D, M>), dim3(grid), dim3(nthr), lds, st,
                        reinterpret_cast<cplx<T>*>(s.amps), reinterpret_cast<cplx<T>*>(lam), g, drounds, nrounds, dops,
-                       reinterpret_cast<const cplx<T>*>(dmats), mat_stride, partial);
+                       reinterpret_cast<const cplx<T>*>(dmats), mat_stride, partial, g.tab);
     return check_launch("stage adjoint rounds");
 }
 

@@ -245,6 +245,7 @@ struct Pass {
     GRef fused{-1, false};   // !tile: the dense block gate
     int seg = 0;             // checkpoint segment
     int round_off = 0, nrounds = 0;  // register rounds (forward); nrounds = 0: op-by-op kernel
+    size_t tab_off = 0;              // register rounds: the pass's geometry table in the list's
     int cr_slot = -1;        // !tile controlled rotation: its index among the list's controlled rotations
 };
 
@@ -253,6 +254,8 @@ struct PassList {
     std::vector<StageOp> hops;
     std::vector<RoundDesc> hrounds;
     RoundDesc* drounds = nullptr;
+    std::vector<uint32_t> htab;      // geometry tables of the passes in register rounds
+    uint32_t* dtab = nullptr;
     std::vector<DevGroup> hgroups;   // bound mode: matrices built on the device
     DevGroup* dgroups = nullptr;
     void* dmats_b = nullptr;         // bound mode: batch x nmats matrices
@@ -274,6 +277,8 @@ struct PassList {
         release_bound();
         if (drounds) (void)hipFree(drounds);
         drounds = nullptr;
+        if (dtab) (void)hipFree(dtab);
+        dtab = nullptr;
         if (dops) (void)hipFree(dops);
         if (dmats) (void)hipFree(dmats);
         if (hmats) (void)hipHostFree(hmats);
@@ -1354,6 +1359,7 @@ static void finalize_passes(const qf_plan* p, PassList& L, bool adjoint) {
     const int D = p->D, n = p->n;
     L.hops.clear();
     L.hrounds.clear();
+    L.htab.clear();
     L.nmats = 0;
     L.nslots = 0;
     L.ncr = 0;
@@ -1434,6 +1440,15 @@ static void finalize_passes(const qf_plan* p, PassList& L, bool adjoint) {
         }
         ps.nops = int(ps.ops.size());
         build_rounds(p, ps, L, dim_of, moff, adjoint);
+        if (ps.nrounds > 0) {
+            std::vector<uint32_t> tab;
+            stage_table(uint32_t(D), adjoint ? adj_group(p) : p->group, ps.geom, tab);
+            ps.geom.use_offhi = ps.geom.io_lanes == 0;
+            for (int i = 0; i < ps.nrounds; ++i)
+                if (L.hrounds[size_t(ps.round_off + i)].need_gidx) ps.geom.use_offhi = 1;
+            ps.tab_off = L.htab.size();
+            L.htab.insert(L.htab.end(), tab.begin(), tab.end());
+        }
         ps.nmat = moff;
         L.nmats += moff;
     }
@@ -1449,6 +1464,12 @@ static qf_status upload_ops(const qf_plan* p, PassList& L) {
         QF_CHECK(dev_malloc(reinterpret_cast<void**>(&L.drounds), L.hrounds.size() * sizeof(RoundDesc), "rounds"));
         QF_HIP_CHECK(hipMemcpy(L.drounds, L.hrounds.data(), L.hrounds.size() * sizeof(RoundDesc),
                                hipMemcpyHostToDevice));
+    }
+    if (!L.htab.empty()) {
+        QF_CHECK(dev_malloc(reinterpret_cast<void**>(&L.dtab), L.htab.size() * sizeof(uint32_t), "stage tables"));
+        QF_HIP_CHECK(hipMemcpy(L.dtab, L.htab.data(), L.htab.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+        for (Pass& ps : L.passes)
+            if (ps.tile && ps.nrounds > 0) ps.geom.tab = L.dtab + ps.tab_off;
     }
     const size_t mb = std::max<size_t>(L.nmats, 1) * esz;
     QF_CHECK(dev_malloc(&L.dmats, mb, "stage matrices"));

@@ -150,6 +150,12 @@ struct StageGeom {
     uint32_t xcd;        // 1: tiles grouped per XCD (tile_of_block), 0: dispatch order
     uint32_t hi_stride[kMaxTileDims];  // global strides of the high tile qudits, most significant first
     uint32_t out_stride[kMaxOuter];    // global strides of the outer qudits, most significant first
+    // register rounds: the pass's geometry table (stage_table) and its parts
+    const uint32_t* tab;               // device
+    uint32_t io_lanes, nstep;          // tile I/O by digits: lanes, steps; io_lanes = 0: by runs
+    uint32_t use_offhi;                // the run offsets are needed in LDS
+    uint32_t t_steps, t_outlo, t_outhi, t_offhi;
+    FastDiv div_ntiles, div_out;
 };
 
 enum StageOpType : int32_t { SOP_U = 0, SOP_SHIFT = 1, SOP_PHASE = 2 };
@@ -260,6 +266,8 @@ qf_status launch_stage_adj_rounds(const StateView& s, void* lam, int M, const St
 qf_status launch_stage_mreduce(double* partial, uint32_t nslots, uint32_t ntiles, uint32_t batch, uint32_t D,
                                double* mout, uint32_t nslots_total, uint32_t slot0, hipStream_t st);
 size_t stage_lds_bytes(const StageGeom& g, int dtype, bool adjoint);
+// Geometry table of a pass in register rounds with groups of M qudits; sets g's table fields but tab.
+void stage_table(uint32_t D, int M, StageGeom& g, std::vector<uint32_t>& out);
 
 }  // namespace qf
 
