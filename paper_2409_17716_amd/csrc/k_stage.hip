@@ -31,6 +31,18 @@ constexpr int kSB = 256;
 
 constexpr int cpow(int b, int e) { return e == 0 ? 1 : b * cpow(b, e - 1); }
 
+// An amplitude as a vector register pair or quad.
+template <typename T>
+struct Vec2;
+template <>
+struct Vec2<float> {
+    typedef float type __attribute__((ext_vector_type(2)));
+};
+template <>
+struct Vec2<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+
 // Workgroup barrier for LDS data only: waits for this wave's LDS operations
 // (lgkmcnt) and meets the other waves, without the fence of __syncthreads that
 // would also wait for every outstanding global load (the pipelined kernel keeps
@@ -96,7 +108,7 @@ constexpr int kIO = 8;
 // offset o inside a run and walks runs, so no per-element division is needed:
 // with R < 256 the lanes form G = 256 / R groups of R (group gr takes runs
 // gr, gr + G, ...); otherwise every lane strides through each run by 256.
-template <typename T, bool LOAD, typename Ref>
+template <typename T, bool LOAD, int ES, typename Ref>
 __device__ __forceinline__ void tile_io_runs(cplx<T>* tile, const StageGeom& g, uint32_t G, uint32_t gr, uint32_t o,
                                              Ref&& at) {
     uint32_t h = gr;
@@ -106,23 +118,23 @@ __device__ __forceinline__ void tile_io_runs(cplx<T>* tile, const StageGeom& g, 
 #pragma unroll
             for (int j = 0; j < kIO; ++j) t[j] = at(h + j * G);
 #pragma unroll
-            for (int j = 0; j < kIO; ++j) tile[(h + j * G) * g.R + o] = t[j];
+            for (int j = 0; j < kIO; ++j) tile[((h + j * G) * g.R + o) * ES] = t[j];
         } else {
 #pragma unroll
-            for (int j = 0; j < kIO; ++j) t[j] = tile[(h + j * G) * g.R + o];
+            for (int j = 0; j < kIO; ++j) t[j] = tile[((h + j * G) * g.R + o) * ES];
 #pragma unroll
             for (int j = 0; j < kIO; ++j) at(h + j * G) = t[j];
         }
     }
     for (; h < g.nhi; h += G) {
         if (LOAD)
-            tile[h * g.R + o] = at(h);
+            tile[(h * g.R + o) * ES] = at(h);
         else
-            at(h) = tile[h * g.R + o];
+            at(h) = tile[(h * g.R + o) * ES];
     }
 }
 
-template <typename T, bool LOAD>
+template <typename T, bool LOAD, int ES = 1>
 __device__ inline void tile_io(cplx<T>* __restrict__ psi, cplx<T>* tile, const StageGeom& g, const uint32_t* offhi,
                                uint32_t base) {
     if (g.R < blockDim.x) {
@@ -134,21 +146,21 @@ __device__ inline void tile_io(cplx<T>* __restrict__ psi, cplx<T>* tile, const S
             // registers below 4 GB: one uniform 64-bit tile pointer and 32-bit
             // byte offsets (scalar-base addressing, one VALU op per access)
             char* pb = reinterpret_cast<char*>(psi + base);
-            tile_io_runs<T, LOAD>(tile, g, G, gr, o, [&](uint32_t h) -> cplx<T>& {
+            tile_io_runs<T, LOAD, ES>(tile, g, G, gr, o, [&](uint32_t h) -> cplx<T>& {
                 return *reinterpret_cast<cplx<T>*>(pb + (offhi[h] + o) * uint32_t(sizeof(cplx<T>)));
             });
             return;
         }
-        tile_io_runs<T, LOAD>(tile, g, G, gr, o, [&](uint32_t h) -> cplx<T>& { return psi[base + offhi[h] + o]; });
+        tile_io_runs<T, LOAD, ES>(tile, g, G, gr, o, [&](uint32_t h) -> cplx<T>& { return psi[base + offhi[h] + o]; });
         return;
     }
     for (uint32_t h = 0; h < g.nhi; ++h) {
         const uint32_t gb = base + offhi[h];
         for (uint32_t o = threadIdx.x; o < g.R; o += blockDim.x) {
             if (LOAD)
-                tile[h * g.R + o] = psi[gb + o];
+                tile[(h * g.R + o) * ES] = psi[gb + o];
             else
-                psi[gb + o] = tile[h * g.R + o];
+                psi[gb + o] = tile[(h * g.R + o) * ES];
         }
     }
 }
@@ -183,27 +195,33 @@ __device__ __forceinline__ void table_offhi(const StageGeom& g, const uint32_t* 
 // one: a global access needs no vector instruction for its address (scalar base
 // plus lane offset) and an LDS access one add, against seven or eight per element
 // for the runs above.  B steps of every tile are in flight.
-template <typename T, int B, bool LOAD, int NT, typename At>
+//
+// ES: the tiles' elements lie ES apart in LDS (2: psi and lam interleaved).
+template <typename T, int B, int ES, bool LOAD, int NT, typename At>
 __device__ __forceinline__ void io_steps(cplx<T>* const (&psi)[NT], cplx<T>* const (&tile)[NT], const StageGeom& g,
                                          const uint32_t* __restrict__ tab, At&& at) {
     const uint32_t* __restrict__ steps = tab + g.t_steps;
+    typedef typename Vec2<T>::type V;
+    V* lt[NT];
+#pragma unroll
+    for (int x = 0; x < NT; ++x) lt[x] = reinterpret_cast<V*>(tile[x]);
     uint32_t e = threadIdx.x;
     for (uint32_t j = 0; j < g.nstep; j += B) {
-        cplx<T> v[NT][B];
+        V v[NT][B];
         if (LOAD) {
 #pragma unroll
             for (int x = 0; x < NT; ++x)
 #pragma unroll
                 for (int c = 0; c < B; ++c) v[x][c] = at(psi[x] + steps[j + c]);
 #pragma unroll
-            for (int x = 0; x < NT; ++x)
+            for (int c = 0; c < B; ++c)
 #pragma unroll
-                for (int c = 0; c < B; ++c) tile[x][e + c * g.io_lanes] = v[x][c];
+                for (int x = 0; x < NT; ++x) lt[x][(e + c * g.io_lanes) * ES] = v[x][c];
         } else {
 #pragma unroll
-            for (int x = 0; x < NT; ++x)
+            for (int c = 0; c < B; ++c)
 #pragma unroll
-                for (int c = 0; c < B; ++c) v[x][c] = tile[x][e + c * g.io_lanes];
+                for (int x = 0; x < NT; ++x) v[x][c] = lt[x][(e + c * g.io_lanes) * ES];
 #pragma unroll
             for (int x = 0; x < NT; ++x)
 #pragma unroll
@@ -216,35 +234,36 @@ __device__ __forceinline__ void io_steps(cplx<T>* const (&psi)[NT], cplx<T>* con
 // The NT tiles' elements from (LOAD) or to the states at psi.  Steps in flight: a
 // power of D (so that it divides the step count), 8 to 25, at most 64 registers;
 // D = 3 with 3 instead of 9: 7.0 against 5.8 ms per forward of 3^16.
-template <typename T, int D, int M, bool LOAD, int NT>
+template <typename T, int D, int M, bool LOAD, int NT, int ES = 1>
 __device__ __forceinline__ void tiles_io(cplx<T>* const (&psi)[NT], cplx<T>* const (&tile)[NT], const StageGeom& g,
                                          const uint32_t* __restrict__ tab, const uint32_t* offhi, uint32_t base,
                                          uint32_t lane_off) {
     if (g.io_lanes == 0) {
 #pragma unroll
-        for (int x = 0; x < NT; ++x) tile_io<T, LOAD>(psi[x], tile[x], g, offhi, base);
+        for (int x = 0; x < NT; ++x) tile_io<T, LOAD, ES>(psi[x], tile[x], g, offhi, base);
         return;
     }
     if (threadIdx.x >= g.io_lanes) return;
     cplx<T>* pb[NT];
 #pragma unroll
     for (int x = 0; x < NT; ++x) pb[x] = psi[x] + base;
+    typedef typename Vec2<T>::type V;
     constexpr int kPow = D == 2 ? 8 : D == 3 ? 9 : D == 4 ? 16 : D == 5 && M == 2 ? 25 : D;
     constexpr int kBig = NT * kPow * int(sizeof(T) / 2) <= 64 ? kPow : D;
     auto run = [&](auto&& at) {
         if (g.nstep % kBig == 0)
-            io_steps<T, kBig, LOAD, NT>(pb, tile, g, tab, at);
+            io_steps<T, kBig, ES, LOAD, NT>(pb, tile, g, tab, at);
         else if (kBig != D && g.nstep % D == 0)
-            io_steps<T, D, LOAD, NT>(pb, tile, g, tab, at);
+            io_steps<T, D, ES, LOAD, NT>(pb, tile, g, tab, at);
         else
-            io_steps<T, 1, LOAD, NT>(pb, tile, g, tab, at);
+            io_steps<T, 1, ES, LOAD, NT>(pb, tile, g, tab, at);
     };
     if (uint64_t(g.N) * sizeof(cplx<T>) <= 0xffffffffull) {
         // registers below 4 GB: scalar base and 32-bit lane offset
         const uint32_t lb = lane_off * uint32_t(sizeof(cplx<T>));
-        run([&](cplx<T>* p) -> cplx<T>& { return *reinterpret_cast<cplx<T>*>(reinterpret_cast<char*>(p) + lb); });
+        run([&](cplx<T>* p) -> V& { return *reinterpret_cast<V*>(reinterpret_cast<char*>(p) + lb); });
     } else {
-        run([&](cplx<T>* p) -> cplx<T>& { return p[lane_off]; });
+        run([&](cplx<T>* p) -> V& { return *reinterpret_cast<V*>(p + lane_off); });
     }
 }
 
@@ -381,10 +400,9 @@ __global__ __launch_bounds__(kSB) void k_stage(cplx<T>* __restrict__ psi, StageG
 template <int D, class F>
 __device__ __forceinline__ double anti_entry(uint32_t e, F&& m) {
     const uint32_t a = e / D, c = e % D;
-    double re0, im0, re1, im1;
-    m(a * D + c, re0, im0);
-    m(c * D + a, re1, im1);
-    return a < c ? 0.5 * (re0 - re1) : 0.5 * (im0 + im1);
+    const bool re = a < c;  // m(j, re): the real or the imaginary part of M's entry j
+    const double x = m(e, re), y = m(c * D + a, re);
+    return re ? 0.5 * (x - y) : 0.5 * (x + y);
 }
 
 // Reverse stage on psi and lam.  Before a U with slot >= 0, lane (entry, part)
@@ -434,12 +452,10 @@ __global__ __launch_bounds__(kSB) void k_stage_adj(cplx<T>* __restrict__ psi, cp
                 __syncthreads();
                 if (int(threadIdx.x) < E)
                     partial[(size_t(op.slot) * nblocks + blk) * E + threadIdx.x] =
-                        anti_entry<D>(threadIdx.x, [&](uint32_t j, double& sr, double& si) {
-                            sr = si = 0.0;
-                            for (int p = 0; p < P; ++p) {
-                                sr += red[0][p * E + j];
-                                si += red[1][p * E + j];
-                            }
+                        anti_entry<D>(threadIdx.x, [&](uint32_t j, bool re) {
+                            double t = 0.0;
+                            for (int p = 0; p < P; ++p) t += red[re ? 0 : 1][p * E + j];
+                            return t;
                         });
                 __syncthreads();
             }
@@ -545,8 +561,9 @@ __device__ constexpr int rdigit(int i) {
 // registers; a REAL one is stored as D * D reals (wide scalar loads: a 10 x 10
 // matrix takes 7 instead of the 100 that its real parts took inside a complex
 // one).
-template <typename T, int D, int M, int J, bool REAL>
-__device__ __forceinline__ void r_u(cplx<T> (&v)[cpow(D, M)], const cplx<T>* __restrict__ U) {
+// NV sub-tiles are multiplied together, so the matrix is read once for them.
+template <typename T, int D, int M, int J, bool REAL, int NV>
+__device__ __forceinline__ void r_u(cplx<T> (&v)[NV][cpow(D, M)], const cplx<T>* __restrict__ U) {
     constexpr int SJ = cpow(D, M - 1 - J);
     constexpr int NF = cpow(D, M - 1);
     // matrices up to 4 x 4 are read once into scalar registers; larger ones
@@ -564,39 +581,46 @@ __device__ __forceinline__ void r_u(cplx<T> (&v)[cpow(D, M)], const cplx<T>* __r
         if constexpr (kCopy) return m[e];
         else return Um[e];
     };
+    // D <= 4: one sub-tile after the other (their matrix stays in registers)
+    constexpr int NP = kCopy ? 1 : NV;
 #pragma unroll
-    for (int c = 0; c < NF; ++c) {
-        const int b0 = (c / SJ) * SJ * D + (c % SJ);
-        cplx<T> y[D];
+    for (int x0 = 0; x0 < NV; x0 += NP)
 #pragma unroll
-        for (int a = 0; a < D; ++a) {
-            if constexpr (REAL) {
-                T re = 0, im = 0;
+        for (int c = 0; c < NF; ++c) {
+            const int b0 = (c / SJ) * SJ * D + (c % SJ);
+            cplx<T> y[NP][D];
+#pragma unroll
+            for (int a = 0; a < D; ++a) {
+#pragma unroll
+                for (int x = 0; x < NP; ++x) y[x][a] = cmake<T>(0, 0);
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    const T w = mat(a * D + d);
-                    re = fma(w, v[b0 + d * SJ].re, re);
-                    im = fma(w, v[b0 + d * SJ].im, im);
+                    const Elem w = mat(a * D + d);
+#pragma unroll
+                    for (int x = 0; x < NP; ++x) {
+                        const cplx<T> z = v[x0 + x][b0 + d * SJ];
+                        if constexpr (REAL) {
+                            y[x][a].re = fma(w, z.re, y[x][a].re);
+                            y[x][a].im = fma(w, z.im, y[x][a].im);
+                        } else {
+                            cmac(y[x][a], w, z);
+                        }
+                    }
                 }
-                y[a] = cmake<T>(re, im);
-            } else {
-                cplx<T> acc = cmake<T>(0, 0);
-#pragma unroll
-                for (int d = 0; d < D; ++d) cmac(acc, mat(a * D + d), v[b0 + d * SJ]);
-                y[a] = acc;
             }
-        }
 #pragma unroll
-        for (int d = 0; d < D; ++d) v[b0 + d * SJ] = y[d];
-    }
+            for (int x = 0; x < NP; ++x)
+#pragma unroll
+                for (int d = 0; d < D; ++d) v[x0 + x][b0 + d * SJ] = y[x][d];
+        }
 }
 
 template <typename T, int D, int M, int J>
-__device__ __forceinline__ void r_u_any(cplx<T> (&v)[cpow(D, M)], const cplx<T>* __restrict__ U, bool real) {
+__device__ __forceinline__ void r_u_any(cplx<T> (&v)[1][cpow(D, M)], const cplx<T>* __restrict__ U, bool real) {
     if (real)
-        r_u<T, D, M, J, true>(v, U);
+        r_u<T, D, M, J, true, 1>(v, U);
     else
-        r_u<T, D, M, J, false>(v, U);
+        r_u<T, D, M, J, false, 1>(v, U);
 }
 
 // CZ factors multiply amplitude x by w^e(x) with e(x) = sum over factors of
@@ -604,9 +628,9 @@ __device__ __forceinline__ void r_u_any(cplx<T> (&v)[cpow(D, M)], const cplx<T>*
 // constant, so e is a quadratic form in the group digits d_j:
 //   e = e0 + sum_j lin_j d_j + sum_{j<l} quad_jl d_j d_l,
 // whose coefficients are accumulated once per sub-tile.
-template <typename T, int D, int M>
-__device__ __forceinline__ void r_phase(cplx<T> (&v)[cpow(D, M)], const StageOp& op, const cplx<T>* __restrict__ mats,
-                               uint32_t gidx0) {
+template <typename T, int D, int M, int NV>
+__device__ __forceinline__ void r_phase(cplx<T> (&v)[NV][cpow(D, M)], const StageOp& op,
+                                          const cplx<T>* __restrict__ mats, uint32_t gidx0) {
     constexpr int DM = cpow(D, M);
     int e0 = 0;
     int lin[M];
@@ -641,7 +665,9 @@ __device__ __forceinline__ void r_phase(cplx<T> (&v)[cpow(D, M)], const StageOp&
 #pragma unroll
             for (int l = j + 1; l < M; ++l) e += quad[j][l] * dj * ((i / cpow(D, M - 1 - l)) % D);
         }
-        v[i] = cmul(v[i], W[e % D]);
+        const cplx<T> ph = W[e % D];
+#pragma unroll
+        for (int x = 0; x < NV; ++x) v[x][i] = cmul(v[x][i], ph);
     }
 }
 
@@ -673,17 +699,6 @@ __device__ __forceinline__ uint32_t rest2_offset(int i, const uint32_t* glsb) {
 
 // LDS access by 32-bit LDS byte address: a tile's base is added once to a
 // sub-tile's base address, not once per access.
-template <typename T>
-struct Vec2;
-template <>
-struct Vec2<float> {
-    typedef float type __attribute__((ext_vector_type(2)));
-};
-template <>
-struct Vec2<double> {
-    typedef double type __attribute__((ext_vector_type(2)));
-};
-
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     return uint32_t(uintptr_t((const __attribute__((address_space(3))) unsigned char*)p));
 }
@@ -834,7 +849,7 @@ __device__ __forceinline__ void store_addrs(uint32_t (&a)[cpow(D, M)], uint32_t 
 }
 
 template <typename T, int D, int M>
-__device__ __forceinline__ void round_ops(cplx<T> (&v)[cpow(D, M)], const RoundDesc& rd, const StageOp* __restrict__ ops,
+__device__ __forceinline__ void round_ops(cplx<T> (&v)[1][cpow(D, M)], const RoundDesc& rd, const StageOp* __restrict__ ops,
                                  const cplx<T>* __restrict__ mats, uint32_t gidx0) {
     for (int oi = rd.op0; oi < rd.op0 + rd.nops; ++oi) {
         const StageOp& op = ops[oi];
@@ -849,7 +864,7 @@ __device__ __forceinline__ void round_ops(cplx<T> (&v)[cpow(D, M)], const RoundD
                 case 4: if constexpr (M > 4) r_u_any<T, D, M, 4>(v, U, real); break;
             }
         } else {
-            r_phase<T, D, M>(v, op, mats, gidx0);
+            r_phase<T, D, M, 1>(v, op, mats, gidx0);
         }
     }
 }
@@ -967,12 +982,10 @@ __device__ __forceinline__ void mreduce_block(MAcc<T, D>& m, double (*red)[kSB],
     }
     __syncthreads();
     if (threadIdx.x < uint32_t(E))
-        out[threadIdx.x] = anti_entry<D>(threadIdx.x, [&](uint32_t j, double& sr, double& si) {
-            sr = si = 0.0;
-            for (uint32_t q = 0; q < nrows; ++q) {
-                sr += red[0][q * E + j];
-                si += red[1][q * E + j];
-            }
+        out[threadIdx.x] = anti_entry<D>(threadIdx.x, [&](uint32_t j, bool re) {
+            double t = 0.0;
+            for (uint32_t q = 0; q < nrows; ++q) t += red[re ? 0 : 1][q * E + j];
+            return t;
         });
     __syncthreads();
 }
@@ -1020,7 +1033,8 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
             // its loads read other lanes' sub-tiles, so every lane loads and
             // multiplies before any lane stores
             const bool act = threadIdx.x < nsub;
-            cplx<T> v[DM];
+            cplx<T> vv[1][DM];
+            cplx<T>(&v)[DM] = vv[0];
             uint32_t tb = 0, gidx0 = 0;
             if (act) {
                 tb = sub_base<D>(dig0, rd);
@@ -1030,9 +1044,9 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
                 add_pre2<D, M>(al, rd, dig0);
 #pragma unroll
                 for (int i = 0; i < DM; ++i) v[i] = lds_ld<T>(al[i]);
-                r_u<T, D, M, 0, false>(v, U0);
+                r_u<T, D, M, 0, false, 1>(vv, U0);
                 asm volatile("" ::: "memory");
-                r_u<T, D, M, 1, false>(v, U1);
+                r_u<T, D, M, 1, false, 1>(vv, U1);
             }
             __syncthreads();
             if (act) {
@@ -1052,7 +1066,8 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
         // the tiles one after the other (one sub-tile live at a time)
 #pragma unroll
         for (int x = 0; x < NT; ++x) {
-            cplx<T> v[DM];
+            cplx<T> vv[1][DM];
+            cplx<T>(&v)[DM] = vv[0];
 #pragma unroll
             for (int i = 0; i < DM; ++i) v[i] = lds_ld<T>(al[i] + dt[x]);
             if constexpr (MACC && NT == 2) {
@@ -1075,34 +1090,34 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
                 for (int i = 0; i < DM; ++i) lds_st<T>(as[i] + dt[x], v[i]);
             };
             if (kind == RK_U0) {
-                r_u<T, D, M, 0, false>(v, U0);
+                r_u<T, D, M, 0, false, 1>(vv, U0);
                 store();
             } else if (kind == RK_U01) {
                 if constexpr (M >= 2) {
-                    r_u<T, D, M, 0, false>(v, U0);
+                    r_u<T, D, M, 0, false, 1>(vv, U0);
                     // keep the second matrix's loads after the first product
                     // (hoisting them would hold both matrices in registers)
                     asm volatile("" ::: "memory");
-                    r_u<T, D, M, 1, false>(v, U1);
+                    r_u<T, D, M, 1, false, 1>(vv, U1);
                 }
                 store();
             } else if (kind == RK_U0_REAL) {
-                r_u<T, D, M, 0, true>(v, U0);
+                r_u<T, D, M, 0, true, 1>(vv, U0);
                 store();
             } else if (kind == RK_U1) {
-                if constexpr (M >= 2) r_u<T, D, M, 1, false>(v, U0);
+                if constexpr (M >= 2) r_u<T, D, M, 1, false, 1>(vv, U0);
                 store();
             } else if (kind == RK_U1_REAL) {
-                if constexpr (M >= 2) r_u<T, D, M, 1, true>(v, U0);
+                if constexpr (M >= 2) r_u<T, D, M, 1, true, 1>(vv, U0);
                 store();
             } else if (kind == RK_PHASE) {
-                r_phase<T, D, M>(v, ops[rd.op0], mats, gidx0);
+                r_phase<T, D, M, 1>(vv, ops[rd.op0], mats, gidx0);
                 store();
             } else if (kind == RK_NONE) {
                 store();
             } else {
                 // generic rounds exist only for groups of 3 or more qudits
-                if constexpr (M >= 3) round_ops<T, D, M>(v, rd, ops, mats, gidx0);
+                if constexpr (M >= 3) round_ops<T, D, M>(vv, rd, ops, mats, gidx0);
                 store();
             }
         }
@@ -1110,6 +1125,95 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
     if constexpr (MACC) {
         if (ma.mslot >= 0)
             mreduce_block<T, D>(macc, ma.red, ma.partial + (size_t(ma.mslot) * gridDim.x + ma.blk) * (D * D));
+    }
+}
+
+// One adjoint round in complex64 on the interleaved tiles (element e: psi at
+// 16 e, lam at 16 e + 8 bytes).  One 16-byte LDS access moves an element of both,
+// so each lane computes one set of addresses, and a U or PHASE is read once for
+// both.  Two tiles taken one after the other computed the store addresses per tile
+// and took a full barrier per part of M (tile_m): D = 5 pass 186 -> 157 us on 5^10,
+// D = 10 1399 -> 1280 us on 10^8, batches of D = 3 / D = 4 registers 121 / 130 ->
+// 108 / 111 us.
+template <int D, int M, bool MACC>
+__device__ __forceinline__ void run_round2(cplx<float>* tile, const StageGeom& g, const uint32_t* offhi, uint32_t base,
+                                           const RoundDesc& rd, const StageOp* __restrict__ ops,
+                                           const cplx<float>* __restrict__ mats, const SubDigits& dig0,
+                                           const MArgs& ma) {
+    constexpr int DM = cpow(D, M);
+    MAcc<float, D> macc;
+    if constexpr (MACC) {
+#pragma unroll
+        for (int e = 0; e < D * D; ++e) macc.re[e] = macc.im[e] = 0.0f;
+    }
+    const uint32_t nsub = g.TE / DM;
+    const uint32_t lb0 = lds_addr(tile);
+    const int kind = rd.kind;
+    const cplx<float>* U0 = mats + rd.mat0;
+    const cplx<float>* U1 = mats + rd.mat1;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) f4 lds_f4;
+    for (uint32_t u = threadIdx.x; u < nsub; u += blockDim.x) {
+        const uint32_t tb = sub_base<D>(u == threadIdx.x ? dig0 : sub_digits<D>(u, rd.nother), rd);
+        const uint32_t gidx0 = rd.need_gidx ? global_index(g, offhi, base, tb) : 0u;
+        cplx<float> v[2][DM];
+        {
+            uint32_t al[DM];
+            load_addrs<D, M>(al, lb0 + tb * 16, rd, gidx0);
+#pragma unroll
+            for (int i = 0; i < DM; ++i) {
+                const f4 x = *(const lds_f4*)uintptr_t(al[i]);
+                v[0][i] = cmake<float>(x.x, x.y);
+                v[1][i] = cmake<float>(x.z, x.w);
+            }
+        }
+        if constexpr (MACC) {
+            if (ma.mslot >= 0) {
+                if (ma.mpos == 0) {
+                    macc_add<float, D, M, 0>(macc, v[0], v[1]);
+                } else {
+                    if constexpr (M >= 2) macc_add<float, D, M, 1>(macc, v[0], v[1]);
+                }
+            }
+        }
+        // each shape stores from its own branch
+        auto store = [&]() {
+            uint32_t as[DM];
+            store_addrs<D, M>(as, lb0 + tb * 16, rd, gidx0);
+#pragma unroll
+            for (int i = 0; i < DM; ++i)
+                *(lds_f4*)uintptr_t(as[i]) = f4{v[0][i].re, v[0][i].im, v[1][i].re, v[1][i].im};
+        };
+        if (kind == RK_U0) {
+            r_u<float, D, M, 0, false, 2>(v, U0);
+            store();
+        } else if (kind == RK_U01) {
+            if constexpr (M >= 2) {
+                r_u<float, D, M, 0, false, 2>(v, U0);
+                // keep the second matrix's loads after the first product
+                asm volatile("" ::: "memory");
+                r_u<float, D, M, 1, false, 2>(v, U1);
+            }
+            store();
+        } else if (kind == RK_U0_REAL) {
+            r_u<float, D, M, 0, true, 2>(v, U0);
+            store();
+        } else if (kind == RK_U1) {
+            if constexpr (M >= 2) r_u<float, D, M, 1, false, 2>(v, U0);
+            store();
+        } else if (kind == RK_U1_REAL) {
+            if constexpr (M >= 2) r_u<float, D, M, 1, true, 2>(v, U0);
+            store();
+        } else if (kind == RK_PHASE) {
+            r_phase<float, D, M, 2>(v, ops[rd.op0], mats, gidx0);
+            store();
+        } else {
+            store();  // permutations only (groups of at most 2 have no generic rounds)
+        }
+    }
+    if constexpr (MACC) {
+        if (ma.mslot >= 0)
+            mreduce_block<float, D>(macc, ma.red, ma.partial + (size_t(ma.mslot) * gridDim.x + ma.blk) * (D * D));
     }
 }
 
@@ -1246,32 +1350,59 @@ __global__ __launch_bounds__(kSB) void k_stage_pipe(cplx<T>* __restrict__ psi, S
     }
 }
 
-// M = sum over the tile's fibres along the op's qudit of psi_f lam_f^dagger,
-// from the LDS tiles, into partial[(slot * nblocks + block) * D*D] (complex
-// FP64).  Lane (block, part) sums a B x B block of entries (B = 2 for even
-// D >= 4: two psi and two lam reads feed four products) over the fibres
-// part, part + P, ... in the state's precision; the parts are then added in
-// FP64 in a fixed order.
-template <typename T, int D>
+// M = sum over the tile's fibres along the op's qudit of psi_f lam_f^dagger, from
+// the LDS tiles, into partial[(slot * nblocks + block) * D*D] (anti_entry form).
+// Lane (block, part) sums a B x B block of entries (B = 2 for even D >= 4: two psi
+// and two lam reads feed four products) over the fibres part, part + P, ... in the
+// state's precision; the parts are then added in FP64 in order.  A fibre's
+// address follows from the last one's by an add and a carry, and the parts meet
+// in LDS (red, MBlock::lds_bytes in complex64) after one barrier.  The tiles'
+// elements lie ES apart.
+template <int D>
+struct MBlock {
+    static constexpr int B = (D % 2 == 0 && D >= 4) ? 2 : 1;
+    static constexpr uint32_t NB = (D / B) * (D / B);
+    static size_t lds_bytes(uint32_t nt) {
+        return nt >= NB ? size_t(nt / NB) * D * D * 2 * sizeof(float) : size_t(D) * D * 2 * sizeof(double);
+    }
+};
+
+template <typename T, int D, int ES>
 __device__ inline void tile_m(const cplx<T>* tp, const cplx<T>* tl, const StageGeom& g, const StageOp& op,
-                              uint32_t blk, double (*red)[kSB], double* __restrict__ partial) {
+                              uint32_t blk, double* red, double* __restrict__ partial) {
     constexpr uint32_t E = D * D;
-    constexpr int B = (D % 2 == 0 && D >= 4) ? 2 : 1;
+    constexpr int B = MBlock<D>::B;
     constexpr uint32_t NBR = D / B, NB = NBR * NBR;
+    constexpr uint32_t ESZ = sizeof(cplx<T>) * ES;  // bytes between elements
     const uint32_t nt = blockDim.x;
     const uint32_t nf = g.TE / D;
+    const uint32_t ls = op.ls, lsb = ls * ESZ;
+    const uint32_t dt = lds_addr(tl) - lds_addr(tp);
     double* out = partial + (size_t(op.slot) * gridDim.x + blk) * E;
     auto block_sum = [&](uint32_t bi, uint32_t f0, uint32_t step, T (&ar)[B * B], T (&ai)[B * B]) {
         const uint32_t a0 = (bi / NBR) * B, c0 = (bi % NBR) * B;
 #pragma unroll
         for (int j = 0; j < B * B; ++j) ar[j] = ai[j] = T(0);
+        // fibre f = hi * ls + lo starts at element hi * D * ls + lo
+        const uint32_t h0 = op.divls.div(f0), dh = op.divls.div(step);
+        uint32_t lo = f0 - h0 * ls;
+        uint32_t ax = lds_addr(tp) + (h0 * uint32_t(D) * ls + lo) * ESZ + a0 * lsb;
+        uint32_t dxy = (c0 - a0) * lsb + dt;  // from the psi to the lam address (mod 2^32)
+        const uint32_t dlo = step - dh * ls, dax = (dh * uint32_t(D) * ls + dlo) * ESZ, wrap = (D - 1) * lsb;
+#pragma unroll 4
         for (uint32_t f = f0; f < nf; f += step) {
-            const uint32_t lb = fibre_lb<D>(op, f);
+            const uint32_t ay = ax + dxy;
             cplx<T> x[B], y[B];
 #pragma unroll
             for (int i = 0; i < B; ++i) {
-                x[i] = tp[lb + (a0 + i) * op.ls];
-                y[i] = tl[lb + (c0 + i) * op.ls];
+                x[i] = lds_ld<T>(ax + i * lsb);
+                y[i] = lds_ld<T>(ay + i * lsb);
+            }
+            ax += dax;
+            lo += dlo;
+            if (lo >= ls) {
+                lo -= ls;
+                ax += wrap;
             }
 #pragma unroll
             for (int i = 0; i < B; ++i)
@@ -1288,13 +1419,33 @@ __device__ inline void tile_m(const cplx<T>* tp, const cplx<T>* tl, const StageG
         const uint32_t bi = threadIdx.x % NB, part = threadIdx.x / NB;
         T ar[B * B], ai[B * B];
         block_sum(bi, part, P, ar, ai);
+        if constexpr (sizeof(T) == 4) {
+            // the parts side by side: [part][re, im][entry]
+            float* parts = reinterpret_cast<float*>(red);
+            if (part < P) {
+#pragma unroll
+                for (int j = 0; j < B * B; ++j) {
+                    parts[(2 * part) * E + entry(bi, j)] = ar[j];
+                    parts[(2 * part + 1) * E + entry(bi, j)] = ai[j];
+                }
+            }
+            __syncthreads();
+            // (the next M's parts are written after the round's barrier)
+            for (uint32_t e = threadIdx.x; e < E; e += nt)
+                out[e] = anti_entry<D>(e, [&](uint32_t j, bool re) {
+                    double t = 0.0;
+                    for (uint32_t q = 0; q < P; ++q) t += double(parts[(2 * q + (re ? 0 : 1)) * E + j]);
+                    return t;
+                });
+            return;
+        }
         for (uint32_t q = 0; q < P; ++q) {
             if (part == q) {
 #pragma unroll
                 for (int j = 0; j < B * B; ++j) {
                     const uint32_t e = entry(bi, j);
-                    red[0][e] = (q ? red[0][e] : 0.0) + double(ar[j]);
-                    red[1][e] = (q ? red[1][e] : 0.0) + double(ai[j]);
+                    red[e] = (q ? red[e] : 0.0) + double(ar[j]);
+                    red[E + e] = (q ? red[E + e] : 0.0) + double(ai[j]);
                 }
             }
             __syncthreads();
@@ -1305,25 +1456,31 @@ __device__ inline void tile_m(const cplx<T>* tp, const cplx<T>* tl, const StageG
             block_sum(bi, 0, 1, ar, ai);
 #pragma unroll
             for (int j = 0; j < B * B; ++j) {
-                red[0][entry(bi, j)] = double(ar[j]);
-                red[1][entry(bi, j)] = double(ai[j]);
+                red[entry(bi, j)] = double(ar[j]);
+                red[E + entry(bi, j)] = double(ai[j]);
             }
         }
         __syncthreads();
     }
     for (uint32_t e = threadIdx.x; e < E; e += nt)
-        out[e] = anti_entry<D>(e, [&](uint32_t j, double& sr, double& si) {
-            sr = red[0][j];
-            si = red[1][j];
-        });
+        out[e] = anti_entry<D>(e, [&](uint32_t j, bool re) { return red[(re ? 0 : E) + j]; });
     __syncthreads();
 }
 
 // Reverse stage in register rounds on psi and lam.  A U that owns an M slot
 // always opens its round, so its M is taken from the LDS tiles before the
 // round's ops run in registers.
+// Wavefronts per SIMD the register count is held to: what the LDS tiles allow at
+// the default tile sizes (D = 3: four workgroups of four wavefronts a CU, D = 10:
+// seven of two; D = 4: two of four).
 template <typename T, int D, int M>
-__global__ __launch_bounds__(kSB) void k_stage_adj_rounds(cplx<T>* __restrict__ psi, cplx<T>* __restrict__ lam,
+constexpr unsigned adj_waves() {
+    if constexpr (sizeof(T) == 4) return M == 2 ? (D <= 3 ? 4 : 2) : D <= 10 ? 4 : 2;
+    return 1;
+}
+
+template <typename T, int D, int M>
+__global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(adj_waves<T, D, M>()))) void k_stage_adj_rounds(cplx<T>* __restrict__ psi, cplx<T>* __restrict__ lam,
                                                           StageGeom g, const RoundDesc* __restrict__ rounds,
                                                           int nrounds, const StageOp* __restrict__ ops,
                                                           const cplx<T>* __restrict__ mats, size_t mat_stride,
@@ -1332,10 +1489,19 @@ __global__ __launch_bounds__(kSB) void k_stage_adj_rounds(cplx<T>* __restrict__ 
     const uint32_t blk = tile_of_block(g);
     mats += size_t(g.div_ntiles.div(blk)) * mat_stride;
     extern __shared__ unsigned char smem[];
+    // complex64: psi and lam interleaved (run_round2); complex128: two tiles
+    constexpr bool kPair = sizeof(T) == 4;
     cplx<T>* tp = reinterpret_cast<cplx<T>*>(smem);
-    cplx<T>* tl = tp + g.TE;
-    uint32_t* offhi = reinterpret_cast<uint32_t*>(tl + g.TE);
-    __shared__ double red[2][kSB];
+    cplx<T>* tl = kPair ? tp + 1 : tp + g.TE;
+    uint32_t* offhi = reinterpret_cast<uint32_t*>(tp + 2 * size_t(g.TE));
+    // sums of M: complex64 with D > 4 after the run offsets, else static
+    double* mred;
+    if constexpr (kPair && D > 4) {
+        mred = reinterpret_cast<double*>(smem + ((2 * size_t(g.TE) * sizeof(cplx<T>) + g.nhi * 4 + 15) & ~size_t(15)));
+    } else {
+        __shared__ double red[2 * kSB];
+        mred = red;
+    }
     const uint4 lane = reinterpret_cast<const uint4*>(tab)[threadIdx.x];
     const uint32_t base = table_base(g, tab, blk);
     if (g.use_offhi) {
@@ -1344,7 +1510,7 @@ __global__ __launch_bounds__(kSB) void k_stage_adj_rounds(cplx<T>* __restrict__ 
     }
     cplx<T>* const st[2] = {psi, lam};
     cplx<T>* const tt[2] = {tp, tl};
-    tiles_io<T, D, M, true, 2>(st, tt, g, tab, offhi, base, lane.x);
+    tiles_io<T, D, M, true, 2, kPair ? 2 : 1>(st, tt, g, tab, offhi, base, lane.x);
     __syncthreads();
     SubDigits dig0;
     dig0.w[0] = lane.y;
@@ -1352,22 +1518,28 @@ __global__ __launch_bounds__(kSB) void k_stage_adj_rounds(cplx<T>* __restrict__ 
     for (int ri = 0; ri < nrounds; ++ri) {
         const RoundDesc& rd = rounds[ri];
         // a slotted U opens its round (never after a leading permutation)
-        MArgs ma;
-        ma.mslot = rd.mslot;
-        ma.mpos = rd.mpos;
         if constexpr (D <= 4) {
             // M from the registers of the round
-            ma.red = red;
+            MArgs ma;
+            ma.mslot = rd.mslot;
+            ma.mpos = rd.mpos;
+            ma.red = reinterpret_cast<double(*)[kSB]>(mred);
             ma.partial = partial;
             ma.blk = blk;
-            run_round<T, D, M, 2, true>(tt, g, offhi, base, rd, ops, mats, dig0, ma);
+            if constexpr (kPair)
+                run_round2<D, M, true>(tp, g, offhi, base, rd, ops, mats, dig0, ma);
+            else
+                run_round<T, D, M, 2, true>(tt, g, offhi, base, rd, ops, mats, dig0, ma);
         } else {
-            if (ma.mslot >= 0) tile_m<T, D>(tp, tl, g, ops[rd.op0], blk, red, partial);
-            run_round<T, D, M, 2>(tt, g, offhi, base, rd, ops, mats, dig0);
+            if (rd.mslot >= 0) tile_m<T, D, kPair ? 2 : 1>(tp, tl, g, ops[rd.op0], blk, mred, partial);
+            if constexpr (kPair)
+                run_round2<D, M, false>(tp, g, offhi, base, rd, ops, mats, dig0, MArgs{});
+            else
+                run_round<T, D, M, 2>(tt, g, offhi, base, rd, ops, mats, dig0);
         }
         __syncthreads();
     }
-    tiles_io<T, D, M, false, 2>(st, tt, g, tab, offhi, base, lane.x);
+    tiles_io<T, D, M, false, 2, kPair ? 2 : 1>(st, tt, g, tab, offhi, base, lane.x);
 }
 
 template <class F>
@@ -1600,8 +1772,9 @@ static qf_status launch_adj_rounds_m(const StateView& s, void* lam, const StageG
                                      int nrounds, const StageOp* dops, const void* dmats, double* partial,
                                      size_t mat_stride, hipStream_t st) {
     const uint32_t grid = g.ntiles * s.batch;
-    const size_t lds = stage_lds_bytes(g, s.dtype, true);
     const uint32_t nthr = rounds_threads(g, cpow(D, M));
+    size_t lds = stage_lds_bytes(g, s.dtype, true);
+    if constexpr (sizeof(T) == 4 && D > 4) lds = ((lds + 15) & ~size_t(15)) + MBlock<D>::lds_bytes(nthr);
     hipLaunchKernelGGL((k_stage_adj_rounds<T, D, M>), dim3(grid), dim3(nthr), lds, st,
                        reinterpret_cast<cplx<T>*>(s.amps), reinterpret_cast<cplx<T>*>(lam), g, drounds, nrounds, dops,
                        reinterpret_cast<const cplx<T>*>(dmats), mat_stride, partial, g.tab);
@@ -1620,7 +1793,7 @@ qf_status launch_stage_adj_rounds(const StateView& s, void* lam, int M, const St
                     return launch_adj_rounds_m<T, D, 1>(s, lam, g, drounds, nrounds, dops, dmats, partial, mat_stride,
                                                         st);
                 case 2:
-                    if constexpr (D <= 5 && (sizeof(T) == 4 || D <= 3))
+                    if constexpr (D <= 3 || (D == 4 && sizeof(T) == 4))
                         return launch_adj_rounds_m<T, D, 2>(s, lam, g, drounds, nrounds, dops, dmats, partial,
                                                             mat_stride, st);
                     break;

@@ -1208,7 +1208,8 @@ static void build_rounds(const qf_plan* p, Pass& ps, PassList& L, const std::vec
         rd.pre0 = pre0;
         rd.pre1 = pre1;
         rd.post = post;
-        const uint32_t esz = p->dtype == QF_C64 ? 8u : 16u;
+        // LDS bytes per element: the complex64 adjoint interleaves psi and lam
+        const uint32_t esz = p->dtype == QF_C64 && !adjoint ? 8u : 16u;
         for (int g = 0; g < M; ++g) {
             rd.gls[g] = ipow(D, k - 1 - grp[g]);
             rd.glsb[g] = rd.gls[g] * esz;

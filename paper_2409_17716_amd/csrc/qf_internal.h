@@ -196,7 +196,7 @@ struct RoundDesc {
     int32_t pre0, pre1, post;       // permutation ops, -1 = none
     int32_t need_gidx;              // some op reads a digit from the global index
     uint32_t gls[kMaxGroup];        // LDS strides of the group qudits, register digit 0 first
-    uint32_t glsb[kMaxGroup];       // the same in bytes (amplitudes of the plan's dtype)
+    uint32_t glsb[kMaxGroup];       // the same in bytes (16 per element where psi and lam are interleaved)
     int32_t nother;                 // k - M
     uint32_t ols[kMaxTileDims];     // LDS strides of the other tile qudits, most significant first
     uint32_t spair[4];              // the last 8 of ols, least significant first, two 16-bit halves per word
