@@ -615,6 +615,70 @@ __device__ __forceinline__ void r_u(cplx<T> (&v)[NV][cpow(D, M)], const cplx<T>*
         }
 }
 
+// One U on a group of one qudit, its result stored to LDS as it is computed: a
+// loop over groups of kRows rows, whose matrix entries (at most 32 words) are read
+// one group ahead.  Unrolled over all rows (r_u) the compiler reads the whole
+// matrix first and spills it to vector lanes: 83 lane moves beside the 400 FMAs of
+// a real 10 x 10 U on two sub-tiles.  store(a, y): row a of every sub-tile.
+template <typename T, int D, bool REAL>
+struct URows {
+    static constexpr int kWords = D * (REAL ? 1 : 2) * int(sizeof(T) / 4);  // of a row
+    static constexpr int rows() {
+        int r = 1;
+        for (int i = 2; i <= D; ++i)
+            if (D % i == 0 && i * kWords <= 32) r = i;
+        return r;
+    }
+    static constexpr int kRows = rows();
+    // matrices that fit the scalar registers take r_u
+    static constexpr bool kUse = D * kWords > 64;
+};
+
+template <typename T, int D, bool REAL, int NV, class Store>
+__device__ __forceinline__ void u_rows(const cplx<T> (&v)[NV][D], const cplx<T>* __restrict__ U, Store&& store) {
+    constexpr int R = URows<T, D, REAL>::kRows, W = R * D * (REAL ? 1 : 2);
+    const T* __restrict__ m = reinterpret_cast<const T*>(U);
+    T cur[W];
+#pragma unroll
+    for (int e = 0; e < W; ++e) cur[e] = m[e];
+#pragma unroll 1
+    for (int a0 = 0; a0 < D; a0 += R) {
+        T nxt[W];
+        const T* __restrict__ mn = m + (a0 + R < D ? (a0 + R) * D * (REAL ? 1 : 2) : 0);
+#pragma unroll
+        for (int e = 0; e < W; ++e) nxt[e] = mn[e];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            cplx<T> y[NV];
+#pragma unroll
+            for (int x = 0; x < NV; ++x) {
+                y[x] = cmake<T>(0, 0);
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    if constexpr (REAL) {
+                        const T w = cur[r * D + d];
+                        y[x].re = fma(w, v[x][d].re, y[x].re);
+                        y[x].im = fma(w, v[x][d].im, y[x].im);
+                    } else {
+                        cmac(y[x], cmake<T>(cur[2 * (r * D + d)], cur[2 * (r * D + d) + 1]), v[x][d]);
+                    }
+                }
+            }
+            store(uint32_t(a0 + r), y);
+        }
+#pragma unroll
+        for (int e = 0; e < W; ++e) cur[e] = nxt[e];
+    }
+}
+
+// LDS byte address to which row a of a sub-tile of a group of one qudit goes (a
+// moved by the round's post permutation, sh of store_shift).
+template <int D>
+__device__ __forceinline__ uint32_t row_addr(uint32_t a, uint32_t sh, uint32_t tbb, uint32_t g0) {
+    const uint32_t o = a + sh;
+    return tbb + __umul24(min(o, o - uint32_t(D)), g0);
+}
+
 template <typename T, int D, int M, int J>
 __device__ __forceinline__ void r_u_any(cplx<T> (&v)[1][cpow(D, M)], const cplx<T>* __restrict__ U, bool real) {
     if (real)
@@ -1089,9 +1153,19 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
 #pragma unroll
                 for (int i = 0; i < DM; ++i) lds_st<T>(as[i] + dt[x], v[i]);
             };
+            [[maybe_unused]] auto store_rows = [&](auto real) {
+                const uint32_t sh = rd.post >= 0 ? lane_shift<D>(rd.perm[2], gidx0) : 0u;
+                u_rows<T, D, decltype(real)::value, 1>(vv, U0, [&](uint32_t a, const cplx<T>(&y)[1]) {
+                    lds_st<T>(row_addr<D>(a, sh, lb0 + tb * ESZ, rd.glsb[0]), y[0]);
+                });
+            };
             if (kind == RK_U0) {
-                r_u<T, D, M, 0, false, 1>(vv, U0);
-                store();
+                if constexpr (M == 1 && NT == 1 && URows<T, D, false>::kUse) {
+                    store_rows(std::false_type{});
+                } else {
+                    r_u<T, D, M, 0, false, 1>(vv, U0);
+                    store();
+                }
             } else if (kind == RK_U01) {
                 if constexpr (M >= 2) {
                     r_u<T, D, M, 0, false, 1>(vv, U0);
@@ -1102,8 +1176,12 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
                 }
                 store();
             } else if (kind == RK_U0_REAL) {
-                r_u<T, D, M, 0, true, 1>(vv, U0);
-                store();
+                if constexpr (M == 1 && NT == 1 && URows<T, D, true>::kUse) {
+                    store_rows(std::true_type{});
+                } else {
+                    r_u<T, D, M, 0, true, 1>(vv, U0);
+                    store();
+                }
             } else if (kind == RK_U1) {
                 if constexpr (M >= 2) r_u<T, D, M, 1, false, 1>(vv, U0);
                 store();
@@ -1184,9 +1262,20 @@ __device__ __forceinline__ void run_round2(cplx<float>* tile, const StageGeom& g
             for (int i = 0; i < DM; ++i)
                 *(lds_f4*)uintptr_t(as[i]) = f4{v[0][i].re, v[0][i].im, v[1][i].re, v[1][i].im};
         };
+        [[maybe_unused]] auto store_rows = [&](auto real) {
+            const uint32_t sh = rd.post >= 0 ? lane_shift<D>(rd.perm[2], gidx0) : 0u;
+            u_rows<float, D, decltype(real)::value, 2>(v, U0, [&](uint32_t a, const cplx<float>(&y)[2]) {
+                *(lds_f4*)uintptr_t(row_addr<D>(a, sh, lb0 + tb * 16, rd.glsb[0])) =
+                    f4{y[0].re, y[0].im, y[1].re, y[1].im};
+            });
+        };
         if (kind == RK_U0) {
-            r_u<float, D, M, 0, false, 2>(v, U0);
-            store();
+            if constexpr (M == 1 && URows<float, D, false>::kUse) {
+                store_rows(std::false_type{});
+            } else {
+                r_u<float, D, M, 0, false, 2>(v, U0);
+                store();
+            }
         } else if (kind == RK_U01) {
             if constexpr (M >= 2) {
                 r_u<float, D, M, 0, false, 2>(v, U0);
@@ -1196,8 +1285,12 @@ __device__ __forceinline__ void run_round2(cplx<float>* tile, const StageGeom& g
             }
             store();
         } else if (kind == RK_U0_REAL) {
-            r_u<float, D, M, 0, true, 2>(v, U0);
-            store();
+            if constexpr (M == 1 && URows<float, D, true>::kUse) {
+                store_rows(std::true_type{});
+            } else {
+                r_u<float, D, M, 0, true, 2>(v, U0);
+                store();
+            }
         } else if (kind == RK_U1) {
             if constexpr (M >= 2) r_u<float, D, M, 1, false, 2>(v, U0);
             store();
