@@ -5,6 +5,8 @@
 // A workgroup owns a tile of NT fibres: it stages X[:, tile] in LDS (reads
 // complete before any write, so the update is in place), then writes
 // B X[:, tile] straight back to HBM.
+#include <algorithm>
+
 #include "qf_internal.h"
 
 namespace qf {
@@ -89,7 +91,7 @@ __global__ __launch_bounds__(kBlock) void k_fused_valu(cplx<T>* __restrict__ psi
 }
 
 // ---------------------------------------------------------------------------
-// FP32 matrix-core path (complex64, K >= 32).  Y = B X with
+// FP32 matrix-core path (complex64, 128 < K <= 256).  Y = B X with
 //   Y_re = B_re X_re - B_im X_im,  Y_im = B_re X_im + B_im X_re
 // on v_mfma_f32_16x16x4f32 (A: 16 x 4, B: 4 x 16, C: 16 x 16).  Lane l of a
 // wavefront supplies A[l % 16][l / 16] and B[l / 16][l % 16] and holds
@@ -173,144 +175,199 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
     }
 }
 
-// Persistent variant for Kp = 16 * NRB <= 128: wave w owns row blocks w and
-// w + 4 and keeps their B fragments for every k step in registers, then loops
-// over fibre tiles (grid-stride), so B is read once per workgroup.
-// Template: NJ column blocks of 16 fibres per tile (NT = 16 NJ fibres; fewer
-// make the LDS tile smaller, so more workgroups share a CU and one's staging
-// overlaps another's products); REAL: the block's imaginary parts are zero,
-// so their fragments are not held.
-template <int NRB, int NJ, bool REAL>
-__global__ __launch_bounds__(kBlock) void k_fused_mfma_regs(cplx<float>* __restrict__ psi,
-                                                            const cplx<float>* __restrict__ B, FusedGeom g) {
-    constexpr int Kp = 16 * NRB;
-    constexpr int KS = Kp / 4;
-    constexpr int RPW = (NRB + 3) / 4;  // row blocks per wave
-    constexpr int NTR = 16 * NJ;        // fibres per tile
-    constexpr int RSR = NTR + 4;        // LDS row stride (floats)
-    typedef float fNJ __attribute__((ext_vector_type(NJ)));
-    extern __shared__ unsigned char smem[];
-    float* xr = reinterpret_cast<float*>(smem);
-    float* xi = xr + size_t(Kp) * RSR;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int lr = lane & 15;
-    const int lk = lane >> 4;
-    float are[RPW][KS];
-    float aim[REAL ? 1 : RPW][REAL ? 1 : KS];
+// ---------------------------------------------------------------------------
+// Blocks of 32 <= K <= 128 in complex64 on the bf16 matrix cores, in FP32
+// precision.  Every FP32 operand is the exact sum of three bf16 values (each the
+// rest of the last one rounded to nearest), and a product keeps the six partial
+// products above 2^-26 of it (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid),
+// exact in the matrix core and added in FP32: 24 v_mfma_f32_16x16x32_bf16 (16
+// cycles each) per 32 complex rows in place of 32 v_mfma_f32_16x16x4f32 (32
+// cycles), and fewer FP32 roundings per sum.  Error against 64 bits (relative,
+// Haar blocks on Gaussian states, also of amplitudes over many decades): K = 32
+// 5.6e-8 (FP32 matrix cores 1.5e-7), K = 49 1.1e-7 (1.8e-7), K = 128 1.9e-7
+// (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  (An infinite amplitude gives NaN where
+// a part of the block is zero.)  HBM-bound up to K = 49; time of a pass against
+// the FP32 cores: K = 49 on 7^9 323 -> 165 us (3.9 TB/s), K = 100 on 10^7 160 ->
+// 83 us (real 125 -> 62), K = 128 on 2^24 290 -> 110 us.
+//
+// A persistent workgroup of NRB wavefronts owns one row block of 16 per wavefront,
+// its block's operands in registers.  A tile of NF fibres lies in LDS as
+// six planes (three parts of the real and imaginary values), a fibre's Kp values
+// contiguous (plus 16 bytes against bank conflicts), so that an operand is one
+// 16-byte read.  The next tile's amplitudes are loaded while the current one is
+// multiplied, then split and stored.
+// ---------------------------------------------------------------------------
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The three bf16 parts of eight floats.
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
 #pragma unroll
-    for (int q = 0; q < RPW; ++q) {
-        const uint32_t arow = uint32_t((wave + 4 * q) * 16 + lr);
+    for (int i = 0; i < 4; ++i) {
+        f32x2 r = {x[2 * i], x[2 * i + 1]};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const uint32_t acol = uint32_t(ks * 4 + lk);
-            cplx<float> a = cmake<float>(0.f, 0.f);
-            if (wave + 4 * q < NRB && arow < g.K && acol < g.K) a = B[arow * g.K + acol];
-            are[q][ks] = a.re;
-            if constexpr (!REAL) aim[q][ks] = a.im;
+        for (int p = 0; p < 3; ++p) {
+            const bf16x2 h = __builtin_convertvector(r, bf16x2);  // to nearest even
+            const uint32_t u = __builtin_bit_cast(uint32_t, h);
+            part[p][i] = u;
+            r.x -= __builtin_bit_cast(float, u << 16);
+            r.y -= __builtin_bit_cast(float, u & 0xffff0000u);
         }
     }
-    const uint32_t ntiles = (g.nfib + NTR - 1) / NTR;
-    for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const uint32_t f0 = tile * NTR;
-        const uint32_t nt = min(uint32_t(NTR), g.nfib - f0);
-        __syncthreads();
-        // X[b][i] goes to position (i % 16) NJ + i / 16 of LDS row b, so that a
-        // lane's NJ column blocks are one read
-        if (g.L == 1) {
-            // nt whole fibres of K contiguous amplitudes: consecutive lanes take
-            // consecutive amplitudes
-            const uint32_t cnt = g.K * nt;
-            const cplx<float>* src = psi + size_t(f0) * g.K;
-            for (uint32_t e = threadIdx.x; e < cnt; e += kBlock) {
-                const uint32_t i = g.divK.div(e);
-                const uint32_t b = e - i * g.K;
-                const cplx<float> v = src[e];
-                const uint32_t pos = b * RSR + (i & 15u) * NJ + (i >> 4);
-                xr[pos] = v.re;
-                xi[pos] = v.im;
-            }
-            // zero the padding: rows past K, columns past nt
-            for (uint32_t e = threadIdx.x; e < uint32_t(Kp * NTR); e += kBlock) {
-                const uint32_t b = e / NTR, i = e - b * NTR;
-                if (b >= g.K || i >= nt) {
-                    const uint32_t pos = b * RSR + (i & 15u) * NJ + (i >> 4);
-                    xr[pos] = 0.f;
-                    xi[pos] = 0.f;
-                }
-            }
-        } else {
-            // a lane keeps one fibre (its base computed once) and takes every
-            // (kBlock / NT)-th row; consecutive lanes take consecutive fibres
-            const uint32_t i = threadIdx.x & (NTR - 1);
-            const bool have = i < nt;
-            const uint32_t fb = have ? fibre_base(g, f0 + i) : 0u;
-            const uint32_t col = (i & 15u) * NJ + (i >> 4);
-            for (uint32_t b = threadIdx.x / NTR; b < uint32_t(Kp); b += kBlock / NTR) {
+}
+
+// Fibres per tile: 64 (512-byte runs of HBM), 32 for K <= 48, where more and
+// smaller workgroups do better (K = 32 on 2^24 amplitudes 54 against 70 us; K = 100
+// on 10^7 108 against 85 us).
+template <int NRB>
+constexpr int split_fibres() {
+    return NRB <= 3 ? 32 : 64;
+}
+
+template <int NRB, bool REAL>
+__global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restrict__ psi,
+                                                          const cplx<float>* __restrict__ B, FusedGeom g) {
+    constexpr int KB = (NRB + 1) / 2;        // k blocks of 32
+    constexpr int Kp = 32 * KB;
+    constexpr int NF = split_fibres<NRB>();
+    constexpr int CS = Kp * 2 + 16;          // bytes between fibres of a plane
+    constexpr int PL = NF * CS;              // bytes of a plane
+    constexpr int NT = 64 * NRB;
+    constexpr int NU = NF * (Kp / 8);        // staging units: 8 rows of one fibre
+    constexpr int UPL = (NU + NT - 1) / NT;  // per lane
+    extern __shared__ unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int lr = lane & 15;  // A row / B column / C column
+    const int lk = lane >> 4;  // eight k of a k block; C row group
+    // the block's rows 16 wave + lr: parts of the real and imaginary entries
+    u32x4 br[KB][3], bi[REAL ? 1 : KB][3];
+    {
+        const uint32_t row = uint32_t(16 * wave + lr);
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            float xr[8], xi[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t col = uint32_t(32 * kb + 8 * lk + i);
                 cplx<float> v = cmake<float>(0.f, 0.f);
-                if (have && b < g.K) v = psi[fb + b * g.L];
-                xr[b * RSR + col] = v.re;
-                xi[b * RSR + col] = v.im;
+                if (row < g.K && col < g.K) v = B[row * g.K + col];
+                xr[i] = v.re;
+                xi[i] = v.im;
+            }
+            split8(xr, br[kb]);
+            if constexpr (!REAL) split8(xi, bi[kb]);
+        }
+    }
+    const uint32_t ntiles = (g.nfib + NF - 1) / NF;
+    cplx<float> x[UPL][8];
+    // unit u: fibre u % NF, rows 8 (u / NF) .. + 7 (consecutive lanes: consecutive
+    // fibres); where fibres are contiguous (L = 1), rows first
+    auto unit = [&](int t, uint32_t& f, uint32_t& k8) {
+        const uint32_t u = threadIdx.x + uint32_t(t) * NT;
+        f = g.L == 1 ? u / (Kp / 8) : u % NF;
+        k8 = g.L == 1 ? u % (Kp / 8) : u / NF;
+        return u < uint32_t(NU);
+    };
+    auto fetch = [&](uint32_t tile) {
+#pragma unroll
+        for (int t = 0; t < UPL; ++t) {
+            uint32_t f, k8;
+            const bool ok = unit(t, f, k8) && tile * NF + f < g.nfib;
+            const uint32_t fb = ok ? fibre_base(g, tile * NF + f) : 0u;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t b = 8 * k8 + i;
+                x[t][i] = cmake<float>(0.f, 0.f);
+                if (ok && b < g.K) x[t][i] = psi[fb + b * g.L];
             }
         }
+    };
+    uint32_t tile = blockIdx.x;
+    if (tile < ntiles) fetch(tile);
+    for (; tile < ntiles; tile += gridDim.x) {
+        __syncthreads();  // the previous tile's operands are read
+#pragma unroll
+        for (int t = 0; t < UPL; ++t) {
+            uint32_t f, k8;
+            if (!unit(t, f, k8)) continue;
+            float v[8];
+            u32x4 part[3];
+            unsigned char* p = smem + f * CS + k8 * 16;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = x[t][i].re;
+            split8(v, part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + q * PL) = part[q];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = x[t][i].im;
+            split8(v, part);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + (3 + q) * PL) = part[q];
+        }
         __syncthreads();
+        if (tile + gridDim.x < ntiles) fetch(tile + gridDim.x);
+        auto mm = [](u32x4 a, u32x4 b, f32x4 c) {
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
+                                                           c, 0, 0, 0);
+        };
 #pragma unroll
-        for (int q = 0; q < RPW; ++q) {
-            const int rb = wave + 4 * q;
-            if (rb >= NRB) continue;
-            f32x4 cr[NJ], ci[NJ];
+        for (int j = 0; j < NF / 16; ++j) {
+            // B_re X_re, B_im X_im, B_re X_im + B_im X_re
+            f32x4 rr = {0.f, 0.f, 0.f, 0.f}, ii = rr, ri = rr;
+            const unsigned char* p = smem + (16 * j + lr) * CS + lk * 16;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                cr[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-                ci[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+            for (int kb = 0; kb < KB; ++kb) {
+                u32x4 xr[3], xi[3];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const fNJ brv = *reinterpret_cast<const fNJ*>(xr + (ks * 4 + lk) * RSR + lr * NJ);
-                const fNJ biv = *reinterpret_cast<const fNJ*>(xi + (ks * 4 + lk) * RSR + lr * NJ);
+                for (int q = 0; q < 3; ++q) {
+                    xr[q] = *reinterpret_cast<const u32x4*>(p + q * PL + kb * 64);
+                    xi[q] = *reinterpret_cast<const u32x4*>(p + (3 + q) * PL + kb * 64);
+                }
+                // smallest partial products first
+                constexpr int pa[6] = {1, 2, 0, 1, 0, 0}, pb[6] = {1, 0, 2, 0, 1, 0};
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const float br = brv[j];
-                    const float bi = biv[j];
-                    cr[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(are[q][ks], br, cr[j], 0, 0, 0);
-                    ci[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(are[q][ks], bi, ci[j], 0, 0, 0);
+                for (int q = 0; q < 6; ++q) {
+                    rr = mm(br[kb][pa[q]], xr[pb[q]], rr);
+                    ri = mm(br[kb][pa[q]], xi[pb[q]], ri);
                     if constexpr (!REAL) {
-                        cr[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(-aim[q][ks], bi, cr[j], 0, 0, 0);
-                        ci[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(aim[q][ks], br, ci[j], 0, 0, 0);
+                        ii = mm(bi[kb][pa[q]], xi[pb[q]], ii);
+                        ri = mm(bi[kb][pa[q]], xr[pb[q]], ri);
                     }
                 }
             }
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const uint32_t col = uint32_t(j * 16 + lr);
-                if (col >= nt) continue;
-                const uint32_t base = fibre_base(g, f0 + col);
+            const uint32_t f = tile * NF + uint32_t(16 * j + lr);
+            if (f < g.nfib) {
+                const uint32_t base = fibre_base(g, f);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const uint32_t row = uint32_t(rb * 16 + 4 * lk + r);
-                    if (row < g.K) psi[base + row * g.L] = cmake<float>(cr[j][r], ci[j][r]);
+                    const uint32_t row = uint32_t(16 * wave + 4 * lk + r);
+                    if (row < g.K) psi[base + row * g.L] = cmake<float>(REAL ? rr[r] : rr[r] - ii[r], ri[r]);
                 }
             }
         }
     }
 }
 
-template <int NRB, int NJ, bool REAL>
-qf_status launch_mfma_regs(const StateView& s, const FusedGeom& g, const void* B, hipStream_t st) {
-    constexpr int NTR = 16 * NJ;
-    const size_t lds = size_t(2) * (16 * NRB) * (NTR + 4) * sizeof(float);
-    const uint32_t ntiles = (g.nfib + NTR - 1) / NTR;
-    const uint32_t grid = ntiles < 4096 ? ntiles : 4096;
-    hipLaunchKernelGGL((k_fused_mfma_regs<NRB, NJ, REAL>), dim3(grid), dim3(kBlock), lds, st,
-                       reinterpret_cast<cplx<float>*>(s.amps), reinterpret_cast<const cplx<float>*>(B), g);
-    return check_launch("qf_apply_fused (matrix cores, persistent)");
-}
-
-// Real blocks: tiles of 32 fibres; complex blocks (twice the products per
-// operand read): 16 (both measured best on the D = 10 and D = 7 pair blocks).
+// The grid fills the LDS of 256 CUs once.
 template <int NRB>
-qf_status launch_mfma_regs_any(const StateView& s, const FusedGeom& g, const void* B, bool real, hipStream_t st) {
-    return real ? launch_mfma_regs<NRB, 2, true>(s, g, B, st) : launch_mfma_regs<NRB, 1, false>(s, g, B, st);
+qf_status launch_split(const StateView& s, const FusedGeom& g, const void* B, bool real, hipStream_t st) {
+    constexpr int Kp = 32 * ((NRB + 1) / 2);
+    constexpr uint32_t NF = split_fibres<NRB>();
+    constexpr size_t lds = size_t(6) * NF * (Kp * 2 + 16);
+    constexpr uint32_t cap = 256 * std::max<uint32_t>(1, uint32_t(160 * 1024 / lds));
+    const uint32_t ntiles = (g.nfib + NF - 1) / NF;
+    const uint32_t grid = std::min(ntiles, cap);
+    auto* amps = reinterpret_cast<cplx<float>*>(s.amps);
+    auto* mat = reinterpret_cast<const cplx<float>*>(B);
+    if (real)
+        hipLaunchKernelGGL((k_fused_split<NRB, true>), dim3(grid), dim3(64 * NRB), lds, st, amps, mat, g);
+    else
+        hipLaunchKernelGGL((k_fused_split<NRB, false>), dim3(grid), dim3(64 * NRB), lds, st, amps, mat, g);
+    return check_launch("qf_apply_fused (bf16 matrix cores)");
 }
 
 }  // namespace
@@ -330,13 +387,13 @@ qf_status launch_fused(const StateView& s, int k, int q0, const void* B, hipStre
     g.divNT.init(nt);
     if (s.dtype == QF_C64 && K >= 32 && K <= 128) {
         switch ((K + 15) / 16) {
-            case 2: return launch_mfma_regs_any<2>(s, g, B, real, st);
-            case 3: return launch_mfma_regs_any<3>(s, g, B, real, st);
-            case 4: return launch_mfma_regs_any<4>(s, g, B, real, st);
-            case 5: return launch_mfma_regs_any<5>(s, g, B, real, st);
-            case 6: return launch_mfma_regs_any<6>(s, g, B, real, st);
-            case 7: return launch_mfma_regs_any<7>(s, g, B, real, st);
-            case 8: return launch_mfma_regs_any<8>(s, g, B, real, st);
+            case 2: return launch_split<2>(s, g, B, real, st);
+            case 3: return launch_split<3>(s, g, B, real, st);
+            case 4: return launch_split<4>(s, g, B, real, st);
+            case 5: return launch_split<5>(s, g, B, real, st);
+            case 6: return launch_split<6>(s, g, B, real, st);
+            case 7: return launch_split<7>(s, g, B, real, st);
+            case 8: return launch_split<8>(s, g, B, real, st);
         }
     }
     if (s.dtype == QF_C64 && K >= 32 && K <= 256) {
