@@ -6,6 +6,7 @@
 //     W = U^dagger (passed in by the host).
 // The reduction is deterministic: fixed per-workgroup tree, then a fixed-order
 // sum over workgroups.
+#include <algorithm>
 #include <type_traits>
 
 #include "qf_internal.h"
@@ -20,132 +21,159 @@ struct MatArgA {
     cplx<T> m[D * D];
 };
 
+// Un-applies one fused run (W: its inverse) on psi and lam along one axis and sums
+// M = sum_f psi_f lam_f^dagger before it in FP64; a row of D * D reals per
+// workgroup holds M's anti-Hermitian part (a * D + c: its real part for a < c, its
+// imaginary part for a >= c).  A shift merged into the run (it came after the run)
+// is undone first, in the addresses of the loads.  Workgroups walk their
+// register's blocks of kFB fibres with their part of M in registers; the rows of
+// many runs are reduced in one launch (a launch per run took 36 x 8.6 us of the
+// 2.1 ms of a 1.7 M-amplitude mixed register's gradient).
 template <typename T, int D>
 __global__ __launch_bounds__(kFB) void k_adj_axis(cplx<T>* __restrict__ psi, cplx<T>* __restrict__ lam,
-                                                  uint32_t nfib_reg, uint32_t blocks_per_reg, uint32_t N,
-                                                  uint32_t L, FastDiv divL, MatArgA<T, D> W,
-                                                  double* __restrict__ partial) {
+                                                  uint32_t nfib_reg, uint32_t blocks_per_reg, uint32_t wgs_per_reg,
+                                                  uint32_t N, uint32_t L, FastDiv divL, MatArgA<T, D> W,
+                                                  ShiftArg sh, double* __restrict__ partial) {
     __shared__ cplx<T> sp[D][kFB];
     __shared__ cplx<T> sl[D][kFB];
-    __shared__ double red[2][kFB];
     constexpr int E = D * D;
-    const uint32_t b = blockIdx.x / blocks_per_reg;
-    const uint32_t blk = blockIdx.x - b * blocks_per_reg;
-    const uint32_t f = blk * kFB + threadIdx.x;
-    const bool live = f < nfib_reg;
-    cplx<T> vp[D], vl[D];
-    if (live) {
-        const uint32_t h = divL.div(f);
-        const uint32_t l = f - h * L;
-        const uint32_t base = b * N + h * (uint32_t(D) * L) + l;
+    constexpr int P = E <= kFB ? kFB / E : 1;     // parts per entry
+    constexpr int NE = E <= kFB ? 1 : (E + kFB - 1) / kFB;  // entries per lane
+    __shared__ double red[2][P * E];
+    const uint32_t b = blockIdx.x / wgs_per_reg;
+    const int e0 = E <= kFB ? threadIdx.x % E : threadIdx.x;
+    const int part = E <= kFB ? threadIdx.x / E : 0;
+    double ar[NE], ai[NE];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            vp[d] = psi[base + uint32_t(d) * L];
-            vl[d] = lam[base + uint32_t(d) * L];
-        }
+    for (int j = 0; j < NE; ++j) ar[j] = ai[j] = 0.0;
+    for (uint32_t blk = blockIdx.x - b * wgs_per_reg; blk < blocks_per_reg; blk += wgs_per_reg) {
+        const uint32_t f = blk * kFB + threadIdx.x;
+        if (f < nfib_reg) {
+            const uint32_t h = divL.div(f);
+            const uint32_t l = f - h * L;
+            const uint32_t base = b * N + h * (uint32_t(D) * L) + l;
+            const uint32_t s = sh.template amount<D>(base);
+            cplx<T> vp[D], vl[D];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            sp[d][threadIdx.x] = vp[d];
-            sl[d][threadIdx.x] = vl[d];
-        }
-        cplx<T> wp[D], wl[D];
+            for (int d = 0; d < D; ++d) {
+                const uint32_t o = base + wrap_add<D>(uint32_t(d), s) * L;
+                vp[d] = psi[o];
+                vl[d] = lam[o];
+            }
 #pragma unroll
-        for (int a = 0; a < D; ++a) {
-            wp[a] = cmake<T>(0, 0);
-            wl[a] = cmake<T>(0, 0);
+            for (int d = 0; d < D; ++d) {
+                sp[d][threadIdx.x] = vp[d];
+                sl[d][threadIdx.x] = vl[d];
+            }
+            cplx<T> wp[D], wl[D];
 #pragma unroll
-            for (int c = 0; c < D; ++c) {
-                cmac(wp[a], W.m[a * D + c], vp[c]);
-                cmac(wl[a], W.m[a * D + c], vl[c]);
+            for (int a = 0; a < D; ++a) {
+                wp[a] = cmake<T>(0, 0);
+                wl[a] = cmake<T>(0, 0);
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    cmac(wp[a], W.m[a * D + c], vp[c]);
+                    cmac(wl[a], W.m[a * D + c], vl[c]);
+                }
+            }
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                psi[base + uint32_t(d) * L] = wp[d];
+                lam[base + uint32_t(d) * L] = wl[d];
+            }
+        } else {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                sp[d][threadIdx.x] = cmake<T>(0, 0);
+                sl[d][threadIdx.x] = cmake<T>(0, 0);
             }
         }
+        __syncthreads();
+        // M[a][c] = sum_i psi_i[a] conj(lam_i[c]); entry e = a * D + c
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            psi[base + uint32_t(d) * L] = wp[d];
-            lam[base + uint32_t(d) * L] = wl[d];
-        }
-    } else {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            sp[d][threadIdx.x] = cmake<T>(0, 0);
-            sl[d][threadIdx.x] = cmake<T>(0, 0);
-        }
-    }
-    __syncthreads();
-    // M[a][c] = sum_i psi_i[a] conj(lam_i[c]); entry e = a*D + c.
-    double* out = partial + size_t(blockIdx.x) * E * 2;
-    if constexpr (E <= kFB) {
-        constexpr int P = kFB / E;  // parts per entry
-        const int e = threadIdx.x % E;
-        const int part = threadIdx.x / E;
-        double ar = 0.0, ai = 0.0;
-        if (part < P) {
+        for (int j = 0; j < NE; ++j) {
+            const int e = e0 + j * kFB;
+            if (part >= P || e >= E) continue;
             const int a = e / D, c = e % D;
+#pragma unroll 4
             for (int i = part; i < kFB; i += P) {
                 const cplx<T> x = sp[a][i];
                 const cplx<T> y = sl[c][i];
-                ar += double(x.re) * double(y.re) + double(x.im) * double(y.im);
-                ai += double(x.im) * double(y.re) - double(x.re) * double(y.im);
+                ar[j] += double(x.re) * double(y.re) + double(x.im) * double(y.im);
+                ai[j] += double(x.im) * double(y.re) - double(x.re) * double(y.im);
             }
         }
-        red[0][threadIdx.x] = ar;
-        red[1][threadIdx.x] = ai;
         __syncthreads();
-        if (threadIdx.x < E) {
-            double sr = 0.0, si = 0.0;
-            for (int p = 0; p < P; ++p) {
-                sr += red[0][p * E + threadIdx.x];
-                si += red[1][p * E + threadIdx.x];
-            }
-            out[2 * threadIdx.x] = sr;
-            out[2 * threadIdx.x + 1] = si;
+    }
+#pragma unroll
+    for (int j = 0; j < NE; ++j) {
+        const int e = e0 + j * kFB;
+        if (part >= P || e >= E) continue;
+        red[0][part * E + e] = ar[j];
+        red[1][part * E + e] = ai[j];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += kFB) {
+        const int a = e / D, c = e % D;
+        const int k = a < c ? 0 : 1;
+        double x = 0.0, y = 0.0;
+        for (int p = 0; p < P; ++p) {
+            x += red[k][p * E + e];
+            y += red[k][p * E + c * D + a];
         }
-    } else {
-        for (int e = threadIdx.x; e < E; e += kFB) {
-            const int a = e / D, c = e % D;
-            double ar = 0.0, ai = 0.0;
-            for (int i = 0; i < kFB; ++i) {
-                const cplx<T> x = sp[a][i];
-                const cplx<T> y = sl[c][i];
-                ar += double(x.re) * double(y.re) + double(x.im) * double(y.im);
-                ai += double(x.im) * double(y.re) - double(x.re) * double(y.im);
-            }
-            out[2 * e] = ar;
-            out[2 * e + 1] = ai;
-        }
+        partial[size_t(blockIdx.x) * E + e] = a < c ? 0.5 * (x - y) : 0.5 * (x + y);
     }
 }
 
-// out[b][slot][e] = sum over the workgroups of register b: one workgroup per
-// (b, e); lanes take workgroups k = lane, lane + 256, ..., then a fixed tree.
-__global__ __launch_bounds__(256) void k_adj_reduce(const double* __restrict__ partial, uint32_t blocks_per_reg,
-                                                    uint32_t E, uint32_t nslots, uint32_t slot, uint32_t slot_elems,
-                                                    double* __restrict__ out) {
-    __shared__ double sh[2][256];
-    const uint32_t b = blockIdx.x / E;
-    const uint32_t e = blockIdx.x - b * E;
-    double sr = 0.0, si = 0.0;
-    for (uint32_t k = threadIdx.x; k < blocks_per_reg; k += 256) {
-        const double* p = partial + (size_t(b) * blocks_per_reg + k) * E * 2;
-        sr += p[2 * e];
-        si += p[2 * e + 1];
-    }
-    sh[0][threadIdx.x] = sr;
-    sh[1][threadIdx.x] = si;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (int(threadIdx.x) < w) {
-            sh[0][threadIdx.x] += sh[0][threadIdx.x + w];
-            sh[1][threadIdx.x] += sh[1][threadIdx.x + w];
+// The rows of up to kAdjRows runs, each summed by one workgroup per register in a
+// fixed order (lane = entry of one of 256 / E rows at a time, eight rows in flight)
+// and written as the complex anti-Hermitian matrix.
+constexpr int kAdjRows = 64;
+
+struct AdjRowsArg {
+    AdjRows run[kAdjRows];
+};
+
+__global__ __launch_bounds__(256) void k_adj_reduce(const double* __restrict__ partial, AdjRowsArg a, uint32_t batch,
+                                                    uint32_t nslots, uint32_t slot_elems, double* __restrict__ out) {
+    __shared__ double red[256];
+    __shared__ double sum[256];
+    const uint32_t r = blockIdx.x / batch, b = blockIdx.x - r * batch;
+    const uint32_t D = a.run[r].D, rows = a.run[r].rows, E = D * D;
+    const double* p = partial + a.run[r].off + size_t(b) * rows * E;
+    const uint32_t G = 256 / E, gr = threadIdx.x / E, e = threadIdx.x - gr * E;
+    constexpr uint32_t kU = 8;
+    double acc = 0.0;
+    if (gr < G) {
+        uint32_t i = gr;
+        for (; i + (kU - 1) * G < rows; i += kU * G) {
+            double x[kU];
+#pragma unroll
+            for (uint32_t u = 0; u < kU; ++u) x[u] = p[size_t(i + u * G) * E + e];
+#pragma unroll
+            for (uint32_t u = 0; u < kU; ++u) acc += x[u];
         }
-        __syncthreads();
+        for (; i < rows; i += G) acc += p[size_t(i) * E + e];
     }
-    if (threadIdx.x == 0) {
-        double* o = out + ((size_t(b) * nslots + slot) * slot_elems + e) * 2;
-        o[0] = sh[0][0];
-        o[1] = sh[1][0];
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    if (threadIdx.x < E) {
+        double t = 0.0;
+        for (uint32_t q = 0; q < G; ++q) t += red[q * E + threadIdx.x];
+        sum[threadIdx.x] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < E) {
+        const uint32_t x = threadIdx.x / D, y = threadIdx.x - x * D;
+        double* o = out + ((size_t(b) * nslots + a.run[r].slot) * slot_elems + threadIdx.x) * 2;
+        o[0] = x == y ? 0.0 : x < y ? sum[x * D + y] : -sum[y * D + x];
+        o[1] = x < y ? sum[y * D + x] : sum[x * D + y];
     }
 }
+
+// Workgroups of a register: at most 2048 rows per run for the reduction (D = 5 on
+// 1.7 M amplitudes: 18.6 us; 640 workgroups 21.4, one per block of fibres 18.7).
+uint32_t adj_axis_wgs(uint32_t bpr) { return std::min(bpr, 2048u); }
 
 template <class F>
 qf_status with_dim_a(uint32_t D, F&& f) {
@@ -171,14 +199,15 @@ qf_status with_dim_a(uint32_t D, F&& f) {
 
 }  // namespace
 
-size_t adj_axis_partial_doubles(const StateView& s) {
-    const uint32_t nfib_reg = s.N / s.dmin;
-    const uint32_t bpr = (nfib_reg + kFB - 1) / kFB;
-    return size_t(bpr) * s.batch * s.dmax * s.dmax * 2;
+AdjRows adj_axis_rows(const StateView& s, int q) {
+    AdjRows r{};
+    r.D = s.dims[q];
+    r.rows = adj_axis_wgs((s.N / r.D + kFB - 1) / kFB);
+    return r;
 }
 
-qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W, double* partial, double* mout,
-                          uint32_t nslots, uint32_t slot, uint32_t slot_elems, hipStream_t st) {
+qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W, double* partial, hipStream_t st,
+                          const ShiftArg* shift) {
     const uint32_t nfib_reg = s.N / s.dims[q];
     const uint32_t bpr = (nfib_reg + kFB - 1) / kFB;
     const uint32_t L = s.strides[q];
@@ -190,20 +219,30 @@ qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W,
         } else {
             MatArgA<T, D> w;
             for (int i = 0; i < D * D; ++i) w.m[i] = cmake<T>(T(W[2 * i]), T(W[2 * i + 1]));
-            hipLaunchKernelGGL((k_adj_axis<T, D>), dim3(bpr * s.batch), dim3(kFB), 0, st,
+            const uint32_t wgs = adj_axis_wgs(bpr);
+            hipLaunchKernelGGL((k_adj_axis<T, D>), dim3(wgs * s.batch), dim3(kFB), 0, st,
                                reinterpret_cast<cplx<T>*>(s.amps), reinterpret_cast<cplx<T>*>(lam), nfib_reg,
-                               bpr, s.N, L, FastDiv(L), w, partial);
-            QF_CHECK(check_launch("adjoint axis"));
-            const uint32_t E = D * D;
-            hipLaunchKernelGGL(k_adj_reduce, dim3(s.batch * E), dim3(256), 0, st, partial, bpr, E, nslots, slot,
-                               slot_elems, mout);
-            return check_launch("adjoint reduce");
+                               bpr, wgs, s.N, L, FastDiv(L), w, shift ? *shift : ShiftArg{}, partial);
+            return check_launch("adjoint axis");
         }
     };
     return with_dim_a(s.dims[q], [&](auto dtag) -> qf_status {
         if (s.dtype == QF_C64) return body(float{}, dtag);
         return body(double{}, dtag);
     });
+}
+
+qf_status launch_adj_reduce(const double* partial, const std::vector<AdjRows>& runs, uint32_t batch, double* mout,
+                            uint32_t nslots, uint32_t slot_elems, hipStream_t st) {
+    for (size_t i = 0; i < runs.size(); i += kAdjRows) {
+        const size_t n = std::min(runs.size() - i, size_t(kAdjRows));
+        AdjRowsArg a{};
+        for (size_t j = 0; j < n; ++j) a.run[j] = runs[i + j];
+        hipLaunchKernelGGL(k_adj_reduce, dim3(uint32_t(n) * batch), dim3(256), 0, st, partial, a, batch, nslots,
+                           slot_elems, mout);
+        QF_CHECK(check_launch("adjoint reduce"));
+    }
+    return QF_OK;
 }
 
 }  // namespace qf

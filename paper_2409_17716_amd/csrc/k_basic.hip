@@ -33,6 +33,7 @@ struct MatArg {
 
 template <typename T, int D>
 struct OpMat {
+    static constexpr bool kMoves = false;
     MatArg<T, D> U;
     __device__ bool skip(uint32_t) const { return false; }
     __device__ void apply(cplx<T> (&v)[D], uint32_t) const {
@@ -49,24 +50,22 @@ struct OpMat {
     }
 };
 
-// x_t -> x_t + shift[x_c] mod D (D = d_t); the control digit is read from
-// the global index of the fibre (any element of the fibre has the same x_c).
+// U and a shift of the same qudit in one sweep: the shift moves amplitudes only, so
+// it is folded into the addresses of the stores (U first) or, for the inverse, of
+// the loads (the shift undone first).
+template <typename T, int D>
+struct OpMatShift : OpMat<T, D> {
+    static constexpr bool kMoves = true;
+    ShiftArg sh;
+    int32_t undo;  // 1: element d loads from d + s, 0: it stores to d + s
+};
+
+// x_t -> x_t + shift[x_c] mod D (D = d_t).
 template <typename T, int D>
 struct OpShift {
-    int32_t shift[kMaxDim];  // per control level, already reduced to [0, D)
-    FastDiv strideC;         // x_c = (index / S_c) mod d_c
-    FastDiv divDc;
-    uint32_t dc;
-    int32_t has_ctrl;
-    __device__ int amount(uint32_t gidx) const {
-        if (!has_ctrl) return shift[0];
-        const uint32_t qv = strideC.div(gidx);
-        const uint32_t c = qv - divDc.div(qv) * dc;
-        int s = shift[0];
-#pragma unroll
-        for (int a = 1; a < kMaxDim; ++a) s = (c == uint32_t(a)) ? shift[a] : s;
-        return s;
-    }
+    static constexpr bool kMoves = false;
+    ShiftArg sh;
+    __device__ int amount(uint32_t gidx) const { return int(sh.template amount<D>(gidx)); }
     __device__ bool skip(uint32_t gidx) const { return amount(gidx) == 0; }
     // v[b] <- v[(b - s) mod D] as a barrel of rotations by 1, 2, 4, ...: every
     // register index is a compile-time constant, so nothing is spilled.
@@ -94,6 +93,7 @@ constexpr int kMaxMcxCtrl = 8;
 
 template <typename T, int D>
 struct OpShiftMulti {
+    static constexpr bool kMoves = false;
     FastDiv strideC[kMaxMcxCtrl];
     FastDiv divDc[kMaxMcxCtrl];  // the controls' dimensions
     int32_t nctrl;
@@ -124,6 +124,22 @@ struct OpShiftMulti {
     }
 };
 
+// The shifts an op folds into a fibre's loads (ls) and stores (ss).
+template <int D, class Op>
+__device__ __forceinline__ void fibre_moves(const Op& op, uint32_t gidx, uint32_t& ls, uint32_t& ss) {
+    if constexpr (Op::kMoves) {
+        const uint32_t s = op.sh.template amount<D>(gidx);
+        ls = op.undo ? s : 0u;
+        ss = op.undo ? 0u : s;
+    }
+}
+
+template <int D, class Op>
+__device__ __forceinline__ uint32_t fibre_slot(int d, uint32_t s) {
+    if constexpr (Op::kMoves) return wrap_add<D>(uint32_t(d), s);
+    else return uint32_t(d);
+}
+
 template <typename T, int D, class Op>
 __global__ __launch_bounds__(kBlock) void k_axis_wide(cplx<T>* __restrict__ psi, uint32_t nfib,
                                                       uint32_t L, FastDiv divL, Op op) {
@@ -133,12 +149,14 @@ __global__ __launch_bounds__(kBlock) void k_axis_wide(cplx<T>* __restrict__ psi,
     const uint32_t l = f - h * L;
     const uint32_t base = h * (uint32_t(D) * L) + l;
     if (op.skip(base)) return;
+    uint32_t ls = 0, ss = 0;
+    fibre_moves<D>(op, base, ls, ss);
     cplx<T> v[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) v[d] = psi[base + uint32_t(d) * L];
+    for (int d = 0; d < D; ++d) v[d] = psi[base + fibre_slot<D, Op>(d, ls) * L];
     op.apply(v, base);
 #pragma unroll
-    for (int d = 0; d < D; ++d) psi[base + uint32_t(d) * L] = v[d];
+    for (int d = 0; d < D; ++d) psi[base + fibre_slot<D, Op>(d, ss) * L] = v[d];
 }
 
 template <typename T, int D, class Op>
@@ -160,12 +178,14 @@ __global__ __launch_bounds__(kBlock) void k_axis_narrow(cplx<T>* __restrict__ ps
     __syncthreads();
     if (threadIdx.x < nf) {
         if (act) {
+            uint32_t ls = 0, ss = 0;
+            fibre_moves<D>(op, start + off, ls, ss);
             cplx<T> v[D];
 #pragma unroll
-            for (int d = 0; d < D; ++d) v[d] = tile[off + uint32_t(d) * L];
+            for (int d = 0; d < D; ++d) v[d] = tile[off + fibre_slot<D, Op>(d, ls) * L];
             op.apply(v, start + off);
 #pragma unroll
-            for (int d = 0; d < D; ++d) tile[off + uint32_t(d) * L] = v[d];
+            for (int d = 0; d < D; ++d) tile[off + fibre_slot<D, Op>(d, ss) * L] = v[d];
         }
     }
     __syncthreads();
@@ -866,7 +886,25 @@ qf_status launch_init(const StateView& s, const std::vector<uint32_t>& index, hi
     });
 }
 
-qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_t st) {
+ShiftArg shift_arg(const StateView& s, int ctrl, int tgt, const int32_t* shift) {
+    ShiftArg a{};
+    const int D = int(s.dims[tgt]), nsh = ctrl < 0 ? 1 : int(s.dims[ctrl]);
+    for (int i = 0; i < nsh; ++i) a.shift[i] = ((shift[i] % D) + D) % D;
+    a.has_ctrl = ctrl >= 0;
+    a.strideC = FastDiv(ctrl >= 0 ? s.strides[ctrl] : 1u);
+    a.dc = ctrl >= 0 ? s.dims[ctrl] : 1u;
+    a.divDc = FastDiv(a.dc);
+    a.mul = -1;
+    for (int m = 0; m < D && a.mul < 0; ++m) {
+        bool ok = true;
+        for (int c = 0; c < nsh; ++c) ok = ok && a.shift[c] == (m * c + a.shift[0]) % D;
+        if (ok) a.mul = m;
+    }
+    return a;
+}
+
+qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_t st, const ShiftArg* shift,
+                          bool undo) {
     return with_type(s.dtype, [&](auto tag) -> qf_status {
         using T = decltype(tag);
         return with_dim(s.dims[q], [&](auto dtag) -> qf_status {
@@ -874,8 +912,18 @@ qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_
             if constexpr (sizeof(MatArg<T, D>) > 2048) {
                 return set_error(QF_ERANGE, "dim %d too large for a complex128 kernel-argument matrix", D);
             } else {
+                auto fill = [&](auto& op) {
+                    for (int i = 0; i < D * D; ++i) op.U.m[i] = cmake<T>(T(U[2 * i]), T(U[2 * i + 1]));
+                };
+                if (shift) {
+                    OpMatShift<T, D> op;
+                    fill(op);
+                    op.sh = *shift;
+                    op.undo = undo;
+                    return run_axis<T, D>(s, q, op, st, "one-qudit gate with a shift");
+                }
                 OpMat<T, D> op;
-                for (int i = 0; i < D * D; ++i) op.U.m[i] = cmake<T>(T(U[2 * i]), T(U[2 * i + 1]));
+                fill(op);
                 return run_axis<T, D>(s, q, op, st, "qf_apply_1q");
             }
         });
@@ -888,15 +936,7 @@ qf_status launch_ctrl(const StateView& s, int ctrl, int tgt, const int32_t* shif
         return with_dim(s.dims[tgt], [&](auto dtag) -> qf_status {
             constexpr int D = decltype(dtag)::value;
             OpShift<T, D> op;
-            const int nsh = ctrl < 0 ? 1 : int(s.dims[ctrl]);
-            for (int i = 0; i < kMaxDim; ++i) {
-                const int v = i < nsh ? shift[i] : 0;
-                op.shift[i] = ((v % D) + D) % D;
-            }
-            op.has_ctrl = ctrl >= 0;
-            op.strideC = FastDiv(ctrl >= 0 ? s.strides[ctrl] : 1u);
-            op.dc = ctrl >= 0 ? s.dims[ctrl] : 1u;
-            op.divDc = FastDiv(op.dc);
+            op.sh = shift_arg(s, ctrl, tgt, shift);
             return run_axis<T, D>(s, tgt, op, st, "qf_apply_ctrl");
         });
     });

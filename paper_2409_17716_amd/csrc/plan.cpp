@@ -28,9 +28,6 @@ namespace qf {
 qf_status make_view(const qf_state* s, StateView& v);
 qf_status combine_terms(const StateView& v, int32_t nterms, const int32_t* term_qudit, const double* term_diag,
                         std::vector<int>& active, std::vector<double>& table);
-size_t adj_axis_partial_doubles(const StateView& s);
-qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W, double* partial, double* mout,
-                          uint32_t nslots, uint32_t slot, uint32_t slot_elems, hipStream_t st);
 
 using cd = std::complex<double>;
 using Mat = std::vector<cd>;  // row-major D x D
@@ -213,6 +210,8 @@ struct Step {
     int slot = -1;           // adjoint M slot
     int cr_slot = -1;        // ST_CROT, slab steps: index among the gradient outputs
     bool slab = false;       // ST_AXIS holding one rotation: run as a two-level slab sweep
+    int shift_gate = -1;     // ST_AXIS: a shift of the same qudit merged into its sweep (after the run)
+    int shift_ctrl = -1;     // its control qudit, -1 = none
 };
 
 // ---------------------------------------------------------------------------
@@ -520,6 +519,54 @@ static void cz_table(int dc, int dt, bool inverse, Mat& out) {
 
 // ---- per-gate schedule ----
 
+static bool step_touches(const qf_plan* p, const Step& s, int q) {
+    if (s.type == ST_FUSED) return q >= s.q && q < s.q + s.k;
+    if (s.type == ST_PERM) {
+        const qf_op& o = p->gates[s.gates[0]].op;
+        if (o.kind == QF_OP_MCX)
+            for (int i = 0; i < o.j; ++i)
+                if (o.shifts[i] == q) return true;
+        return o.q1 == q || (o.kind == QF_OP_SWAP && o.q0 == q);
+    }
+    return s.q == q || s.q2 == q || (s.shift_gate >= 0 && s.shift_ctrl == q);
+}
+
+// Merges a shift (X, CSUM, controlled shift) into the sweep of the last run on its
+// target, where no step between them touches its target or control: it then moves
+// before those steps (it only relabels the amplitudes they work on, so every
+// rounding stays as it was) and becomes an address offset of that sweep.  Of the
+// 24 sweeps of a layer of runs and a CSUM ring on 12 qudits, 13 remain.
+static void merge_shifts(qf_plan* p) {
+    std::vector<Step> out;
+    for (Step& s : p->steps) {
+        int host = -1;
+        if (s.type == ST_CTRL)
+            for (int j = int(out.size()) - 1; j >= 0; --j) {
+                const Step& t = out[size_t(j)];
+                if (t.type == ST_AXIS && t.q == s.q && !t.slab && t.shift_gate < 0) {
+                    host = j;
+                    break;
+                }
+                if (step_touches(p, t, s.q) || (s.q2 >= 0 && step_touches(p, t, s.q2))) break;
+            }
+        if (host < 0) {
+            out.push_back(std::move(s));
+            continue;
+        }
+        out[size_t(host)].shift_gate = s.gates[0];
+        out[size_t(host)].shift_ctrl = s.q2;
+    }
+    p->steps.swap(out);
+}
+
+// The merged shift of an ST_AXIS step (forward amounts).
+static ShiftArg step_shift(const qf_plan* p, const Step& s, const StateView& v) {
+    int32_t sh[kMaxDim] = {};
+    const int nc = s.shift_ctrl >= 0 ? p->dims[s.shift_ctrl] : 1;
+    for (int c = 0; c < nc; ++c) sh[c] = shift_of(p->gates[s.shift_gate].op, c, p->dims[s.q]);
+    return shift_arg(v, s.shift_ctrl, s.q, sh);
+}
+
 static void build_steps(qf_plan* p) {
     std::vector<std::vector<int>> pending(p->n);
     auto flush = [&](int q) {
@@ -595,13 +642,15 @@ static void build_steps(qf_plan* p) {
         p->steps.push_back(s);
     }
     for (int q = 0; q < p->n; ++q) flush(q);
+    for (auto& s : p->steps)
+        s.slab = s.type == ST_AXIS && s.gates.size() == 1 && is_rot(p->gates[s.gates[0]].op.kind);
+    if (!per_gate) merge_shifts(p);
     p->nslots = 0;
     p->ncr_steps = 0;
     for (auto& s : p->steps) {
         // a step of one lone rotation runs as a slab sweep: it reads and writes
         // only the levels the rotation moves, and its gradient comes straight
         // from the slab adjoint kernel
-        s.slab = s.type == ST_AXIS && s.gates.size() == 1 && is_rot(p->gates[s.gates[0]].op.kind);
         if (s.type == ST_AXIS && s.has_param && !s.slab) s.slot = p->nslots++;
         if (s.type == ST_CROT || s.slab) s.cr_slot = p->ncr_steps++;
     }
@@ -632,6 +681,10 @@ static qf_status run_step(const qf_plan* p, const Step& s, const StateView& v, c
             if (inverse) U = dagger(U, p->dims[s.q]);
             std::vector<double> buf;
             to_interleaved(U, buf);
+            if (s.shift_gate >= 0) {
+                const ShiftArg sh = step_shift(p, s, v);
+                return launch_apply_1q(v, s.q, buf.data(), st, &sh, inverse);
+            }
             return launch_apply_1q(v, s.q, buf.data(), st);
         }
         case ST_CTRL: {
@@ -1601,6 +1654,10 @@ static qf_status prof_end(qf_plan* p, hipStream_t st, hipEvent_t a, int family, 
     return QF_OK;
 }
 
+// FP64 values of partial M sums the per-gate reverse walk collects before it
+// reduces them (64 MB; one run's rows where they alone are more).
+constexpr size_t kAdjPartial = size_t(8) << 20;
+
 // ---- checkpoints ----
 
 static size_t state_bytes(const StateView& v) { return size_t(v.total) * (v.dtype == QF_C64 ? 8 : 16); }
@@ -2019,7 +2076,13 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
         for (const Pass& ps : plan->rev.passes)
             if (ps.tile) pdoubles = std::max(pdoubles, size_t(ps.nslots) * ps.geom.ntiles * v.batch * E);
     } else {
-        pdoubles = std::max<size_t>(adj_axis_partial_doubles(v), 1);
+        // the rows of all runs, within kAdjPartial
+        for (const Step& s : plan->steps)
+            if (s.slot >= 0) {
+                const AdjRows r = adj_axis_rows(v, s.q);
+                const size_t need = size_t(r.rows) * r.D * r.D * v.batch;
+                pdoubles = std::max(need, std::min(pdoubles + need, kAdjPartial));
+            }
     }
     const int ncr = stg ? plan->rev.ncr : plan->ncr_steps;
     if (ncr > 0) pdoubles = std::max(pdoubles, crot_partial_doubles(v));
@@ -2073,8 +2136,19 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
             if (e == hipSuccess) plan->rev.done_valid = true;
         }
     } else if (rs == QF_OK) {
+        std::vector<AdjRows> runs;  // summed together when their rows fill the buffer, and at the end
+        size_t used = 0;
+        auto reduce_runs = [&]() {
+            if (rs == QF_OK)
+                rs = launch_adj_reduce(partial, runs, v.batch, mdev, uint32_t(plan->nslots), uint32_t(E), st);
+            runs.clear();
+            used = 0;
+        };
         for (int si = int(plan->steps.size()) - 1; si >= 0 && rs == QF_OK; --si) {
             const Step& s = plan->steps[si];
+            // the controlled-rotation kernels take the buffer for their own sums
+            if ((s.type == ST_AXIS && s.slab) || s.type == ST_CROT) reduce_runs();
+            if (rs != QF_OK) break;
             if (s.type == ST_AXIS && s.slab) {
                 const qf_op so = slab_op(plan->gates[s.gates[0]].op);
                 std::vector<double> tab;
@@ -2087,9 +2161,18 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
                 to_interleaved(W, buf);
                 hipEvent_t a;
                 rs = prof_begin(plan, st, &a);
+                ShiftArg sh{};
+                if (s.shift_gate >= 0) sh = step_shift(plan, s, v);
+                AdjRows r = adj_axis_rows(v, s.q);
+                const size_t need = size_t(r.rows) * r.D * r.D * v.batch;
+                if (used + need > pdoubles) reduce_runs();
+                r.off = used;
+                r.slot = uint32_t(s.slot);
+                used += need;
+                runs.push_back(r);
                 if (rs == QF_OK)
-                    rs = launch_adj_axis(v, lam->amps, s.q, buf.data(), partial, mdev, plan->nslots, s.slot,
-                                         uint32_t(E), st);
+                    rs = launch_adj_axis(v, lam->amps, s.q, buf.data(), partial + r.off, st,
+                                         s.shift_gate >= 0 ? &sh : nullptr);
                 if (rs == QF_OK) rs = prof_end(plan, st, a, F_ADJ_AXIS, 4.0 * state_bytes(v));
             } else if (s.type == ST_CROT) {
                 const qf_op& o = plan->gates[s.gates[0]].op;
@@ -2102,6 +2185,7 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
                 if (rs == QF_OK) rs = run_step(plan, s, vl, theta, true, st);
             }
         }
+        reduce_runs();
     }
     std::vector<double> mhost(mcount), crhost(crcount, 0.0);
     if (rs == QF_OK && nslots > 0) {
@@ -2729,7 +2813,6 @@ qf_status qf_adjoint_grad_dev(qf_plan* plan, const qf_state* psi, const qf_state
     for (size_t i = 0; i < table_re.size(); ++i) table_re[i] = table[2 * i];
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const int D = plan->D;
-    const size_t E = size_t(D) * D;
     const size_t esz = plan->dtype == QF_C64 ? 8 : 16;
     if (loss) QF_CHECK(launch_expect_ws(v, active, table, loss, plan->w_expect, st));
     if (!seed) QF_CHECK(launch_diag_observable(v, lam->amps, active, table_re, st));

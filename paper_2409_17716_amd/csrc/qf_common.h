@@ -90,6 +90,36 @@ struct FastDiv {
     }
 };
 
+// A controlled shift x_t -> x_t + shift[x_c] mod d_t of a fibre along its target.
+// The control digit is read from the global index of the fibre (any element of
+// it has the same x_c).
+struct ShiftArg {
+    int32_t shift[16];  // per control level, already reduced to [0, d_t)
+    FastDiv strideC;    // x_c = (index / S_c) mod d_c
+    FastDiv divDc;
+    uint32_t dc;
+    int32_t has_ctrl;   // 0: shift[0] for every fibre
+    int32_t mul;        // shift[c] = (mul * c + shift[0]) mod d_t (CSUM: mul = 1), or -1 if not of that form
+    template <int D>    // D = d_t
+    __device__ uint32_t amount(uint32_t gidx) const {
+        if (!has_ctrl) return uint32_t(shift[0]);
+        const uint32_t qv = strideC.div(gidx);
+        const uint32_t c = qv - divDc.div(qv) * dc;
+        if (mul >= 0) return (uint32_t(mul) * c + uint32_t(shift[0])) % uint32_t(D);
+        int s = shift[0];
+#pragma unroll
+        for (int a = 1; a < 16; ++a) s = (c == uint32_t(a)) ? shift[a] : s;
+        return uint32_t(s);
+    }
+};
+
+// (d + s) mod D for d, s in [0, D)
+template <int D>
+__device__ __forceinline__ uint32_t wrap_add(uint32_t d, uint32_t s) {
+    const uint32_t t = d + s;
+    return min(t, t - uint32_t(D));
+}
+
 }  // namespace qf
 
 // ---------------------------------------------------------------------------

@@ -62,7 +62,11 @@ inline uint32_t span(const StateView& s, int q0, int k) {
 
 // ---- per-gate launchers (k_basic.hip) ----
 qf_status launch_init(const StateView& s, const std::vector<uint32_t>& index, hipStream_t st);
-qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_t st);
+ShiftArg shift_arg(const StateView& s, int ctrl, int tgt, const int32_t* shift);
+// shift: a controlled shift of the same qudit in the same sweep, after U, or
+// (undo) its inverse before U.
+qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_t st, const ShiftArg* shift = nullptr,
+                          bool undo = false);
 qf_status launch_ctrl(const StateView& s, int ctrl, int tgt, const int32_t* shift, hipStream_t st);
 qf_status launch_diag(const StateView& s, int k, const int32_t* qudits, const double* phases,
                       hipStream_t st);
@@ -94,6 +98,22 @@ qf_status launch_expect_noalloc(const StateView& s, const std::vector<int>& acti
 // table value (the Hermitian part of a diagonal observable).
 qf_status launch_diag_observable(const StateView& psi, void* lam_amps, const std::vector<int>& active,
                                  const std::vector<double>& table_re, hipStream_t st);
+
+// ---- reverse sweep of a fused run along one axis (k_adjoint.hip) ----
+// The partial M sums of one run: rows of D * D reals per register, batch * rows of
+// them from partial + off on.
+struct AdjRows {
+    uint64_t off;
+    uint32_t rows, D, slot;
+};
+AdjRows adj_axis_rows(const StateView& s, int q);  // rows and D
+// W: the run's inverse; shift: a shift merged into the run, undone first; partial:
+// the run's rows.
+qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W, double* partial, hipStream_t st,
+                          const ShiftArg* shift);
+// mout[(b * nslots + slot) * slot_elems]: M of every listed run (complex D x D).
+qf_status launch_adj_reduce(const double* partial, const std::vector<AdjRows>& runs, uint32_t batch, double* mout,
+                            uint32_t nslots, uint32_t slot_elems, hipStream_t st);
 
 // ---- controlled rotation (k_crot.hip) ----
 // sum_m |m><m|_ctrl (x) R(m theta)_tgt; kind 0 = x, 1 = y, 2 = z type; with
