@@ -745,13 +745,6 @@ __device__ __forceinline__ uint32_t rest_offset(int i, const uint32_t* glsb) {
     return o;
 }
 
-// (d + s) mod D for d, s in [0, D)
-template <int D>
-__device__ __forceinline__ uint32_t add_mod(uint32_t d, uint32_t s) {
-    const uint32_t t = d + s;
-    return t >= uint32_t(D) ? t - uint32_t(D) : t;
-}
-
 // LDS byte offset of register i over group positions 2 .. M-1.
 template <int D, int M>
 __device__ __forceinline__ uint32_t rest2_offset(int i, const uint32_t* glsb) {
@@ -825,12 +818,12 @@ __device__ __forceinline__ void load_addrs(uint32_t (&a)[cpow(D, M)], uint32_t t
             uint32_t od[D];
             const uint32_t s0 = rd.pre0 >= 0 ? neg_mod<D>(lane_shift<D>(rd.perm[0], gidx0)) : 0u;
 #pragma unroll
-            for (int d = 0; d < D; ++d) od[d] = tbb + __umul24(add_mod<D>(uint32_t(d), s0), g0);
+            for (int d = 0; d < D; ++d) od[d] = tbb + __umul24(wrap_add<D>(uint32_t(d), s0), g0);
             const uint32_t g1 = rd.glsb[1];
 #pragma unroll
             for (int i = 0; i < DM; ++i) {
                 const int d0 = rdigit<D, M, 0>(i);
-                const uint32_t e1 = add_mod<D>(uint32_t(rdigit<D, M, 1>(i)), neg_mod<D>(uint32_t(rd.perm[1].shifts[d0])));
+                const uint32_t e1 = wrap_add<D>(uint32_t(rdigit<D, M, 1>(i)), neg_mod<D>(uint32_t(rd.perm[1].shifts[d0])));
                 a[i] = od[d0] + (e1 * g1 + rest2_offset<D, M>(i, rd.glsb));
             }
             return;
@@ -847,7 +840,7 @@ __device__ __forceinline__ void load_addrs(uint32_t (&a)[cpow(D, M)], uint32_t t
 #pragma unroll
             for (int i = 0; i < DM; ++i) {
                 const uint32_t s = neg_mod<D>(uint32_t(P.shifts[rdigit<D, M, 1>(i)]));
-                a[i] = tbb + (add_mod<D>(uint32_t(rdigit<D, M, 0>(i)), s) * g0 + rest_offset<D, M>(i, rd.glsb));
+                a[i] = tbb + (wrap_add<D>(uint32_t(rdigit<D, M, 0>(i)), s) * g0 + rest_offset<D, M>(i, rd.glsb));
             }
             return;
         }
@@ -855,7 +848,7 @@ __device__ __forceinline__ void load_addrs(uint32_t (&a)[cpow(D, M)], uint32_t t
     const uint32_t s = neg_mod<D>(lane_shift<D>(P, gidx0));
     uint32_t od[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) od[d] = tbb + __umul24(add_mod<D>(uint32_t(d), s), g0);
+    for (int d = 0; d < D; ++d) od[d] = tbb + __umul24(wrap_add<D>(uint32_t(d), s), g0);
 #pragma unroll
     for (int i = 0; i < DM; ++i) a[i] = od[rdigit<D, M, 0>(i)] + rest_offset<D, M>(i, rd.glsb);
 }
@@ -878,7 +871,7 @@ __device__ __forceinline__ void add_pre2(uint32_t (&a)[cpow(D, M)], const RoundD
     const uint32_t ls = rd.pre2_lsb;
     uint32_t o2[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) o2[d] = (add_mod<D>(xt, neg_mod<D>(uint32_t(rd.pre2_shifts[d]))) - xt) * ls;
+    for (int d = 0; d < D; ++d) o2[d] = (wrap_add<D>(xt, neg_mod<D>(uint32_t(rd.pre2_shifts[d]))) - xt) * ls;
 #pragma unroll
     for (int i = 0; i < DM; ++i) a[i] += o2[rdigit<D, M, 1>(i)];
 }
@@ -899,7 +892,7 @@ __device__ __forceinline__ void store_addrs(uint32_t (&a)[cpow(D, M)], uint32_t 
 #pragma unroll
             for (int i = 0; i < DM; ++i) {
                 const uint32_t s = uint32_t(P.shifts[rdigit<D, M, 1>(i)]);
-                a[i] = tbb + (add_mod<D>(uint32_t(rdigit<D, M, 0>(i)), s) * g0 + rest_offset<D, M>(i, rd.glsb));
+                a[i] = tbb + (wrap_add<D>(uint32_t(rdigit<D, M, 0>(i)), s) * g0 + rest_offset<D, M>(i, rd.glsb));
             }
             return;
         }
@@ -907,7 +900,7 @@ __device__ __forceinline__ void store_addrs(uint32_t (&a)[cpow(D, M)], uint32_t 
     const uint32_t s = lane_shift<D>(P, gidx0);
     uint32_t od[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) od[d] = tbb + __umul24(add_mod<D>(uint32_t(d), s), g0);
+    for (int d = 0; d < D; ++d) od[d] = tbb + __umul24(wrap_add<D>(uint32_t(d), s), g0);
 #pragma unroll
     for (int i = 0; i < DM; ++i) a[i] = od[rdigit<D, M, 0>(i)] + rest_offset<D, M>(i, rd.glsb);
 }
