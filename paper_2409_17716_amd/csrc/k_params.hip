@@ -3,6 +3,7 @@
 // FP64 (the same closed forms as the host builder) and need no host work, so a
 // forward + adjoint step can be captured in a HIP graph and replayed with new
 // angles.
+#include <cstring>
 #include <type_traits>
 
 #include "qf_internal.h"
@@ -89,6 +90,15 @@ __device__ inline void dm_apply_gate(const DevGate& g, const double* theta, bool
             return;
         }
     }
+}
+
+// A few host words into device memory by kernel argument.
+constexpr int kPutWords = 960;
+struct PutArg {
+    uint32_t w[kPutWords];
+};
+__global__ __launch_bounds__(256) void k_put(uint32_t* __restrict__ dst, uint32_t n, PutArg a) {
+    for (uint32_t i = threadIdx.x; i < n; i += 256) dst[i] = a.w[i];
 }
 
 template <typename T, int D>
@@ -310,6 +320,15 @@ qf_status with_dim_p(int D, F&& f) {
 }
 
 }  // namespace
+
+bool put_fits(size_t bytes) { return bytes <= sizeof(PutArg) && bytes % 4 == 0; }
+
+qf_status launch_put(void* dst, const void* src, size_t bytes, hipStream_t st) {
+    PutArg a;
+    std::memcpy(a.w, src, bytes);
+    hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(dst), uint32_t(bytes / 4), a);
+    return check_launch("matrix upload");
+}
 
 qf_status launch_build_mats(int D, int dtype, const DevGroup* groups, int ngroups, const DevGate* gates,
                             const double* theta, int64_t theta_stride, uint32_t batch, void* mats, size_t mat_stride,

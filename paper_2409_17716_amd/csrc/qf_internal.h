@@ -314,6 +314,10 @@ struct DevGradGroup {
     int32_t c0;        // first contribution slot (one per rotation of the run)
 };
 
+// bytes of host memory to device memory by kernel argument (put_fits: at most 3840
+// bytes): one launch, and src may be reused at once.
+bool put_fits(size_t bytes);
+qf_status launch_put(void* dst, const void* src, size_t bytes, hipStream_t st);
 qf_status launch_build_mats(int D, int dtype, const DevGroup* groups, int ngroups, const DevGate* gates,
                             const double* theta, int64_t theta_stride, uint32_t batch, void* mats, size_t mat_stride,
                             hipStream_t st);
