@@ -12,7 +12,8 @@
 // a wavefront is one contiguous run.  The forward kernel gives each lane
 // kFPL fibres, kCB apart, and issues all their loads before the first store:
 // with one fibre a wavefront keeps only 1 KB of loads in flight when the two
-// levels are contiguous slabs, too little to cover the HBM latency.
+// levels are contiguous slabs, too little to cover the HBM latency.  A register
+// whose fibres make fewer than two workgroups a CU that way takes one per lane.
 //
 // Per control level m the kernels read a two-entry table: x, y types
 // (cos(m theta / 2), sin(m theta / 2)) in one complex entry (the inverse
@@ -21,6 +22,7 @@
 //   m * Im <lam_f| S |psi_f>   (the slab generator is m S)
 // over its fibres in FP64 (fixed tree per workgroup, then a fixed-order sum per
 // register) and un-applies the gate on psi and lam.
+#include <algorithm>
 #include <type_traits>
 
 #include "qf_internal.h"
@@ -29,7 +31,7 @@ namespace qf {
 namespace {
 
 constexpr int kCB = 256;
-constexpr int kFPL = 4;  // fibres per lane in the forward kernel
+constexpr int kFPL = 4;  // fibres per lane in the forward kernel (large registers)
 
 struct CrGeom {
     int32_t has_ctrl;    // 0: plain rotation, every fibre uses table entry 1
@@ -41,7 +43,7 @@ struct CrGeom {
     uint32_t nfib;       // fibres per register, N / d_t
     uint32_t N;          // amplitudes per register
     uint32_t bpr;        // workgroups per register (one fibre per lane: the adjoint)
-    uint32_t bprf;       // workgroups per register of the forward kernel (kFPL fibres per lane)
+    uint32_t bprf;       // workgroups per register of the forward kernel with kFPL fibres per lane
     int32_t kind;        // 0 = x, 1 = y, 2 = z
     int32_t j, k;        // levels (z: j)
     double alpha;        // z: sqrt(2 / (j (j + 1)))
@@ -66,48 +68,44 @@ __device__ __forceinline__ uint32_t ctrl_level(const CrGeom& g, uint32_t local) 
 }
 
 // The x- or y-type rotation of levels (j, k) with cs = (cos, sin) of half the
-// angle, on the pair (a, b) = (psi_j, psi_k).
-template <typename T>
+// angle, on the pair (a, b) = (psi_j, psi_k).  The fused operations are written out
+// (which product of a sum is rounded first), so that every kernel variant of a
+// direction gives the same bits.
+template <typename T, bool ADJ>
 __device__ __forceinline__ void rot_pair(int kind, cplx<T> cs, cplx<T>& a, cplx<T>& b) {
     const T c = cs.re, s = cs.im;
     const cplx<T> x = a, y = b;
     if (kind == 0) {  // [[c, -i s], [-i s, c]]
-        a = cmake<T>(c * x.re + s * y.im, c * x.im - s * y.re);
-        b = cmake<T>(c * y.re + s * x.im, c * y.im - s * x.re);
+        a = cmake<T>(fma(s, y.im, c * x.re), fma(c, x.im, -(s * y.re)));
+        b = cmake<T>(ADJ ? fma(c, y.re, s * x.im) : fma(s, x.im, c * y.re), fma(c, y.im, -(s * x.re)));
     } else {          // [[c, -s], [s, c]]
-        a = cmake<T>(c * x.re - s * y.re, c * x.im - s * y.im);
-        b = cmake<T>(s * x.re + c * y.re, s * x.im + c * y.im);
+        a = cmake<T>(fma(-s, y.re, c * x.re), fma(c, x.im, -(s * y.im)));
+        b = ADJ ? cmake<T>(fma(c, y.re, s * x.re), fma(c, y.im, s * x.im))
+                : cmake<T>(fma(s, x.re, c * y.re), fma(s, x.im, c * y.im));
     }
 }
 
-// Applies the table's rotation for control level m to the fibre at base.
-template <typename T, int D>
-__device__ __forceinline__ void rotate(cplx<T>* __restrict__ psi, const CrGeom& g, uint32_t base, const cplx<T>* tab,
-                                       uint32_t m) {
-    if (g.kind == 2) {
-        const cplx<T> p1 = tab[2 * m], p2 = tab[2 * m + 1];
-        for (int d = 0; d < g.j; ++d) psi[base + uint32_t(d) * g.L] = cmul(psi[base + uint32_t(d) * g.L], p1);
-        psi[base + uint32_t(g.j) * g.L] = cmul(psi[base + uint32_t(g.j) * g.L], p2);
-        return;
-    }
-    const uint32_t ia = base + uint32_t(g.j) * g.L, ib = base + uint32_t(g.k) * g.L;
-    cplx<T> a = psi[ia], b = psi[ib];
-    rot_pair<T>(g.kind, tab[2 * m], a, b);
-    psi[ia] = a;
-    psi[ib] = b;
+// The z-type rotation of control level m on the fibre at base.
+template <typename T>
+__device__ __forceinline__ void rotate_z(cplx<T>* __restrict__ psi, const CrGeom& g, uint32_t base,
+                                         const cplx<T>* tab, uint32_t m) {
+    const cplx<T> p1 = tab[2 * m], p2 = tab[2 * m + 1];
+    for (int d = 0; d < g.j; ++d) psi[base + uint32_t(d) * g.L] = cmul(psi[base + uint32_t(d) * g.L], p1);
+    psi[base + uint32_t(g.j) * g.L] = cmul(psi[base + uint32_t(g.j) * g.L], p2);
 }
 
-template <typename T, int D>
+template <typename T, int D, int FPL>
 __global__ __launch_bounds__(kCB) void k_crot(cplx<T>* __restrict__ psi, CrGeom g, CrTab<T> harg,
                                               const cplx<T>* __restrict__ dtab, size_t tab_stride) {
     __shared__ cplx<T> tab[2 * kMaxDim];
-    const uint32_t b = blockIdx.x / g.bprf;
+    const uint32_t wgs = FPL == 1 ? g.bpr : g.bprf;
+    const uint32_t b = blockIdx.x / wgs;
     load_tab<T>(harg, dtab, tab_stride, b, g.ntab, tab);
-    const uint32_t f0 = (blockIdx.x - b * g.bprf) * (kCB * kFPL) + threadIdx.x;
+    const uint32_t f0 = (blockIdx.x - b * wgs) * (kCB * FPL) + threadIdx.x;
     cplx<T>* const p = psi + size_t(b) * g.N;
-    uint32_t loc[kFPL], lev[kFPL];  // fibre base and control level (0: left alone)
+    uint32_t loc[FPL], lev[FPL];  // fibre base and control level (0: left alone)
 #pragma unroll
-    for (int i = 0; i < kFPL; ++i) {
+    for (int i = 0; i < FPL; ++i) {
         const uint32_t f = f0 + uint32_t(i) * kCB;
         loc[i] = 0;
         lev[i] = 0;
@@ -119,14 +117,14 @@ __global__ __launch_bounds__(kCB) void k_crot(cplx<T>* __restrict__ psi, CrGeom 
     }
     if (g.kind == 2) {
 #pragma unroll
-        for (int i = 0; i < kFPL; ++i)
-            if (lev[i] != 0) rotate<T, D>(p, g, loc[i], tab, lev[i]);
+        for (int i = 0; i < FPL; ++i)
+            if (lev[i] != 0) rotate_z<T>(p, g, loc[i], tab, lev[i]);
         return;
     }
     const uint32_t oj = uint32_t(g.j) * g.L, ok = uint32_t(g.k) * g.L;
-    cplx<T> va[kFPL], vb[kFPL];
+    cplx<T> va[FPL], vb[FPL];
 #pragma unroll
-    for (int i = 0; i < kFPL; ++i) {
+    for (int i = 0; i < FPL; ++i) {
         va[i] = cmake<T>(0, 0);
         vb[i] = cmake<T>(0, 0);
         if (lev[i] != 0) {
@@ -135,31 +133,36 @@ __global__ __launch_bounds__(kCB) void k_crot(cplx<T>* __restrict__ psi, CrGeom 
         }
     }
 #pragma unroll
-    for (int i = 0; i < kFPL; ++i) {
+    for (int i = 0; i < FPL; ++i) {
         if (lev[i] == 0) continue;
-        rot_pair<T>(g.kind, tab[2 * lev[i]], va[i], vb[i]);
+        rot_pair<T, false>(g.kind, tab[2 * lev[i]], va[i], vb[i]);
         p[loc[i] + oj] = va[i];
         p[loc[i] + ok] = vb[i];
     }
 }
 
-// Deterministic workgroup sum (fixed tree).
+// Deterministic workgroup sum: an xor butterfly inside each wavefront, then the
+// wavefront totals in order.
 __device__ inline double cr_block_sum(double v, double* sh) {
-    sh[threadIdx.x] = v;
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+    if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int w = kCB / 2; w > 0; w >>= 1) {
-        if (int(threadIdx.x) < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    return sh[0];
+    double r = sh[0];
+#pragma unroll
+    for (int w = 1; w < kCB / 64; ++w) r += sh[w];
+    return r;
 }
 
+// psi and lam are read once: the gradient term and the rotation take the loaded
+// amplitudes (with the rotation loading them again, its latency came on top of the
+// gradient's: 5.4 us against 4.4 on 4^9 in complex128).
 template <typename T, int D>
 __global__ __launch_bounds__(kCB) void k_crot_adj(cplx<T>* __restrict__ psi, cplx<T>* __restrict__ lam, CrGeom g,
                                                   CrTab<T> harg, const cplx<T>* __restrict__ dtab, size_t tab_stride,
                                                   double* __restrict__ partial) {
     __shared__ cplx<T> tab[2 * kMaxDim];
-    __shared__ double sh[kCB];
+    __shared__ double sh[kCB / 64];
     const uint32_t b = blockIdx.x / g.bpr;
     load_tab<T>(harg, dtab, tab_stride, b, g.ntab, tab);
     const uint32_t f = (blockIdx.x - b * g.bpr) * kCB + threadIdx.x;
@@ -173,39 +176,67 @@ __global__ __launch_bounds__(kCB) void k_crot_adj(cplx<T>* __restrict__ psi, cpl
             cplx<T>* l = lam + size_t(b) * g.N;
             double im = 0.0;  // Im <lam_f| S |psi_f>
             if (g.kind == 2) {
+                const cplx<T> p1 = tab[2 * m], p2 = tab[2 * m + 1];
                 for (int d = 0; d <= g.j; ++d) {
-                    const cplx<T> x = p[local + uint32_t(d) * g.L], y = l[local + uint32_t(d) * g.L];
+                    const uint32_t i = local + uint32_t(d) * g.L;
+                    const cplx<T> x = p[i], y = l[i];
                     const double w = d < g.j ? g.alpha : -g.alpha * g.j;
                     im += w * (double(y.re) * double(x.im) - double(y.im) * double(x.re));
+                    const cplx<T> ph = d < g.j ? p1 : p2;
+                    p[i] = cmul(x, ph);
+                    l[i] = cmul(y, ph);
                 }
             } else {
                 const uint32_t ia = local + uint32_t(g.j) * g.L, ib = local + uint32_t(g.k) * g.L;
-                const cplx<T> pj = p[ia], pk = p[ib], lj = l[ia], lk = l[ib];
+                cplx<T> pj = p[ia], pk = p[ib], lj = l[ia], lk = l[ib];
                 // conj(lj) pk and conj(lk) pj
                 const double r1 = double(lj.re) * pk.re + double(lj.im) * pk.im;
                 const double i1 = double(lj.re) * pk.im - double(lj.im) * pk.re;
                 const double r2 = double(lk.re) * pj.re + double(lk.im) * pj.im;
                 const double i2 = double(lk.re) * pj.im - double(lk.im) * pj.re;
                 im = g.kind == 0 ? i1 + i2 : r2 - r1;  // x: Im(z1 + z2); y: Im(-i z1 + i z2)
+                rot_pair<T, true>(g.kind, tab[2 * m], pj, pk);
+                rot_pair<T, true>(g.kind, tab[2 * m], lj, lk);
+                p[ia] = pj;
+                p[ib] = pk;
+                l[ia] = lj;
+                l[ib] = lk;
             }
             acc = double(m) * im;
-            rotate<T, D>(p, g, local, tab, m);
-            rotate<T, D>(l, g, local, tab, m);
         }
     }
     const double s = cr_block_sum(acc, sh);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// out[b * ostride] = sum of the bpr partials of register b (fixed order).
-__global__ __launch_bounds__(kCB) void k_crot_reduce(const double* __restrict__ partial, uint32_t bpr,
-                                                     double* __restrict__ out, uint32_t ostride) {
-    __shared__ double sh[kCB];
-    const uint32_t b = blockIdx.x;
-    double s = 0.0;
-    for (uint32_t i = threadIdx.x; i < bpr; i += kCB) s += partial[size_t(b) * bpr + i];
-    s = cr_block_sum(s, sh);
-    if (threadIdx.x == 0) out[size_t(b) * ostride] = s;
+// out[b * ostride + a.gate[r].out] = sum of the partials of gate r and register b
+// (fixed order), for up to kCrotRows gates in one launch.
+constexpr int kCrotRows = 128;
+
+struct CrotRowsArg {
+    CrotRows gate[kCrotRows];
+};
+
+__global__ __launch_bounds__(kCB) void k_crot_reduce(const double* __restrict__ partial, CrotRowsArg a,
+                                                     uint32_t batch, double* __restrict__ out, uint32_t ostride) {
+    __shared__ double sh[kCB / 64];
+    const uint32_t r = blockIdx.x / batch, b = blockIdx.x - r * batch;
+    const uint32_t bpr = a.gate[r].rows;
+    const double* p = partial + a.gate[r].off + size_t(b) * bpr;
+    constexpr int kAcc = 8;  // independent loads in flight per lane
+    double acc[kAcc];
+#pragma unroll
+    for (int j = 0; j < kAcc; ++j) acc[j] = 0.0;
+    for (uint32_t i = threadIdx.x; i < bpr; i += kAcc * kCB)
+#pragma unroll
+        for (int j = 0; j < kAcc; ++j)
+            if (i + j * kCB < bpr) acc[j] += p[i + j * kCB];
+#pragma unroll
+    for (int w = kAcc / 2; w > 0; w >>= 1)
+#pragma unroll
+        for (int j = 0; j < w; ++j) acc[j] += acc[j + w];
+    const double s = cr_block_sum(acc[0], sh);
+    if (threadIdx.x == 0) out[size_t(b) * ostride + a.gate[r].out] = s;
 }
 
 template <class F>
@@ -259,30 +290,36 @@ CrTab<T> host_tab(const double* htab, uint32_t ntab) {
 
 }  // namespace
 
-size_t crot_partial_doubles(const StateView& s) {
-    const uint32_t nfib = s.N / s.dmin;
-    return size_t((nfib + kCB - 1) / kCB) * s.batch;
-}
+uint32_t crot_rows(const StateView& s, int tgt) { return (s.N / s.dims[tgt] + kCB - 1) / kCB; }
 
 qf_status launch_crot(const StateView& s, const CrotArgs& a, const void* dtab, size_t tab_stride, const double* htab,
                       hipStream_t st) {
     const CrGeom g = make_geom(s, a);
+    // 64 workgroups of four fibres per lane left a 4^9 register's launch at 4.8 us
+    const bool one = uint64_t(g.bprf) * s.batch < 512;
     return with_dim_c(s.dims[a.tgt], [&](auto dtag) -> qf_status {
         constexpr int D = decltype(dtag)::value;
+        auto go = [&](auto tag) {
+            using T = decltype(tag);
+            auto* amps = reinterpret_cast<cplx<T>*>(s.amps);
+            auto* tab = reinterpret_cast<const cplx<T>*>(dtab);
+            if (one)
+                hipLaunchKernelGGL((k_crot<T, D, 1>), dim3(g.bpr * s.batch), dim3(kCB), 0, st, amps, g,
+                                   host_tab<T>(htab, g.ntab), tab, tab_stride);
+            else
+                hipLaunchKernelGGL((k_crot<T, D, kFPL>), dim3(g.bprf * s.batch), dim3(kCB), 0, st, amps, g,
+                                   host_tab<T>(htab, g.ntab), tab, tab_stride);
+        };
         if (s.dtype == QF_C64)
-            hipLaunchKernelGGL((k_crot<float, D>), dim3(g.bprf * s.batch), dim3(kCB), 0, st,
-                               reinterpret_cast<cplx<float>*>(s.amps), g, host_tab<float>(htab, g.ntab),
-                               reinterpret_cast<const cplx<float>*>(dtab), tab_stride);
+            go(float{});
         else
-            hipLaunchKernelGGL((k_crot<double, D>), dim3(g.bprf * s.batch), dim3(kCB), 0, st,
-                               reinterpret_cast<cplx<double>*>(s.amps), g, host_tab<double>(htab, g.ntab),
-                               reinterpret_cast<const cplx<double>*>(dtab), tab_stride);
+            go(double{});
         return check_launch("controlled rotation");
     });
 }
 
 qf_status launch_crot_adj(const StateView& s, void* lam, const CrotArgs& a, const void* dtab, size_t tab_stride,
-                          const double* htab, double* partial, double* out, uint32_t ostride, hipStream_t st) {
+                          const double* htab, double* partial, hipStream_t st) {
     const CrGeom g = make_geom(s, a);
     return with_dim_c(s.dims[a.tgt], [&](auto dtag) -> qf_status {
         constexpr int D = decltype(dtag)::value;
@@ -296,10 +333,20 @@ qf_status launch_crot_adj(const StateView& s, void* lam, const CrotArgs& a, cons
                                reinterpret_cast<cplx<double>*>(s.amps), reinterpret_cast<cplx<double>*>(lam), g,
                                host_tab<double>(htab, g.ntab), reinterpret_cast<const cplx<double>*>(dtab), tab_stride,
                                partial);
-        QF_CHECK(check_launch("controlled rotation adjoint"));
-        hipLaunchKernelGGL(k_crot_reduce, dim3(s.batch), dim3(kCB), 0, st, partial, g.bpr, out, ostride);
-        return check_launch("controlled rotation gradient sum");
+        return check_launch("controlled rotation adjoint");
     });
+}
+
+qf_status launch_crot_reduce(const double* partial, const std::vector<CrotRows>& gates, uint32_t batch, double* out,
+                             uint32_t ostride, hipStream_t st) {
+    for (size_t i = 0; i < gates.size(); i += kCrotRows) {
+        const size_t n = std::min(gates.size() - i, size_t(kCrotRows));
+        CrotRowsArg a{};
+        for (size_t j = 0; j < n; ++j) a.gate[j] = gates[i + j];
+        hipLaunchKernelGGL(k_crot_reduce, dim3(uint32_t(n) * batch), dim3(kCB), 0, st, partial, a, batch, out, ostride);
+        QF_CHECK(check_launch("controlled rotation gradient sums"));
+    }
+    return QF_OK;
 }
 
 }  // namespace qf

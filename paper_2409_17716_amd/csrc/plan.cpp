@@ -331,15 +331,18 @@ struct qf_plan {
     double* w_m = nullptr;
     double* w_contrib = nullptr;
     double* w_expect = nullptr;
+    double* w_crot = nullptr;         // partial sums of the reverse controlled rotations
+    size_t w_crot_cap = 0;
     void release_bound() {
         for (void* q : {static_cast<void*>(dgates), static_cast<void*>(dgg), static_cast<void*>(d_poff),
                         static_cast<void*>(d_plist), static_cast<void*>(w_partial), static_cast<void*>(w_m),
-                        static_cast<void*>(w_contrib), static_cast<void*>(w_expect)})
+                        static_cast<void*>(w_contrib), static_cast<void*>(w_expect), static_cast<void*>(w_crot)})
             if (q) (void)hipFree(q);
         dgates = nullptr;
         dgg = nullptr;
         d_poff = d_plist = nullptr;
-        w_partial = w_m = w_contrib = w_expect = nullptr;
+        w_partial = w_m = w_contrib = w_expect = w_crot = nullptr;
+        w_crot_cap = 0;
         fwd.release_bound();
         rev.release_bound();
         bound = 0;
@@ -385,6 +388,8 @@ struct qf_plan {
         std::swap(w_m, o.w_m);
         std::swap(w_contrib, o.w_contrib);
         std::swap(w_expect, o.w_expect);
+        std::swap(w_crot, o.w_crot);
+        std::swap(w_crot_cap, o.w_crot_cap);
     }
     ~qf_plan() {
         release_bound();
@@ -1658,9 +1663,45 @@ static qf_status prof_end(qf_plan* p, hipStream_t st, hipEvent_t a, int family, 
     return QF_OK;
 }
 
-// FP64 values of partial M sums the per-gate reverse walk collects before it
-// reduces them (64 MB; one run's rows where they alone are more).
+// FP64 values of partial sums (M rows of per-gate runs, sums of controlled
+// rotations) that a reverse walk collects before it reduces them in one launch
+// (64 MB; those of one gate where they alone are more).
 constexpr size_t kAdjPartial = size_t(8) << 20;
+
+// Partial sums of the reverse walk's controlled rotations, reduced together when
+// the buffer is full and at the end.
+struct CrotSums {
+    double* buf = nullptr;
+    size_t cap = 0, used = 0;
+    std::vector<CrotRows> gates;
+    uint32_t batch = 1;
+    double* out = nullptr;
+    uint32_t ostride = 0;
+    hipStream_t st = nullptr;
+
+    // values for ncr gates of a register whose sweeps have at most rows workgroups
+    static size_t capacity(size_t ncr, const StateView& v) {
+        uint32_t rows = 1;
+        for (uint32_t q = 0; q < v.n; ++q) rows = std::max(rows, crot_rows(v, int(q)));
+        const size_t per = size_t(rows) * v.batch;
+        return std::max(per, std::min(per * ncr, kAdjPartial));
+    }
+    qf_status flush() {
+        const qf_status r = launch_crot_reduce(buf, gates, batch, out, ostride, st);
+        gates.clear();
+        used = 0;
+        return r;
+    }
+    qf_status run(const StateView& v, void* lam, const CrotArgs& a, const void* dtab, size_t tab_stride,
+                  const double* htab, int slot) {
+        const size_t need = size_t(crot_rows(v, a.tgt)) * v.batch;
+        if (used + need > cap) QF_CHECK(flush());
+        QF_CHECK(launch_crot_adj(v, lam, a, dtab, tab_stride, htab, buf + used, st));
+        gates.push_back(CrotRows{used, crot_rows(v, a.tgt), uint32_t(slot)});
+        used += need;
+        return QF_OK;
+    }
+};
 
 // ---- checkpoints ----
 
@@ -2089,18 +2130,24 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
             }
     }
     const int ncr = stg ? plan->rev.ncr : plan->ncr_steps;
-    if (ncr > 0) pdoubles = std::max(pdoubles, crot_partial_doubles(v));
+    CrotSums cr;
+    cr.cap = ncr > 0 ? CrotSums::capacity(size_t(ncr), v) : 0;
     double* partial = nullptr;
     double* mdev = nullptr;
-    double* crout = nullptr;
+    double* crout = nullptr;  // the gradients, then the partial sums
     const size_t mcount = size_t(v.batch) * std::max(nslots, 1) * E * 2;
     const size_t crcount = size_t(v.batch) * std::max(ncr, 1);
     qf_status rs = dev_malloc_async(reinterpret_cast<void**>(&partial), pdoubles * sizeof(double), st,
                                     "adjoint partial sums");
     if (rs == QF_OK) rs = dev_malloc_async(reinterpret_cast<void**>(&mdev), mcount * sizeof(double), st, "adjoint M");
     if (rs == QF_OK && ncr > 0)
-        rs = dev_malloc_async(reinterpret_cast<void**>(&crout), crcount * sizeof(double), st,
+        rs = dev_malloc_async(reinterpret_cast<void**>(&crout), (crcount + cr.cap) * sizeof(double), st,
                               "controlled-rotation gradients");
+    if (crout) cr.buf = crout + crcount;
+    cr.batch = v.batch;
+    cr.out = crout;
+    cr.ostride = uint32_t(ncr);
+    cr.st = st;
     // lam = H_O psi with H_O the Hermitian part of O (seed mode: lam already holds the seed)
     if (rs == QF_OK && !seed) rs = launch_diag_observable(v, lam->amps, active, table_re, st);
     if (rs == QF_OK && stg) {
@@ -2127,8 +2174,7 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
                 hipEvent_t a;
                 rs = prof_begin(plan, st, &a);
                 if (rs == QF_OK)
-                    rs = launch_crot_adj(v, lam->amps, crot_args(plan->gates[ps.fused.gi].op), tab, 0, nullptr,
-                                         partial, crout + ps.cr_slot, uint32_t(ncr), st);
+                    rs = cr.run(v, lam->amps, crot_args(plan->gates[ps.fused.gi].op), tab, 0, nullptr, ps.cr_slot);
                 if (rs == QF_OK) rs = prof_end(plan, st, a, F_CROT_ADJ, 4.0 * state_bytes(v) * 2.0 / D);
             } else {
                 rs = run_fused_pass(plan, plan->rev, ps, v, st);
@@ -2150,15 +2196,11 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
         };
         for (int si = int(plan->steps.size()) - 1; si >= 0 && rs == QF_OK; --si) {
             const Step& s = plan->steps[si];
-            // the controlled-rotation kernels take the buffer for their own sums
-            if ((s.type == ST_AXIS && s.slab) || s.type == ST_CROT) reduce_runs();
-            if (rs != QF_OK) break;
             if (s.type == ST_AXIS && s.slab) {
                 const qf_op so = slab_op(plan->gates[s.gates[0]].op);
                 std::vector<double> tab;
                 crot_table(so, ctrl_levels(plan, so), theta, true, tab);
-                rs = launch_crot_adj(v, lam->amps, crot_args(so), nullptr, 0, tab.data(), partial, crout + s.cr_slot,
-                                     uint32_t(ncr), st);
+                rs = cr.run(v, lam->amps, crot_args(so), nullptr, 0, tab.data(), s.cr_slot);
             } else if (s.type == ST_AXIS && s.has_param) {
                 Mat W = dagger(step_matrix(plan, s, theta), plan->dims[s.q]);
                 std::vector<double> buf;
@@ -2182,8 +2224,7 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
                 const qf_op& o = plan->gates[s.gates[0]].op;
                 std::vector<double> tab;
                 crot_table(o, ctrl_levels(plan, o), theta, true, tab);
-                rs = launch_crot_adj(v, lam->amps, crot_args(o), nullptr, 0, tab.data(), partial, crout + s.cr_slot,
-                                     uint32_t(ncr), st);
+                rs = cr.run(v, lam->amps, crot_args(o), nullptr, 0, tab.data(), s.cr_slot);
             } else {
                 rs = run_step(plan, s, v, theta, true, st);
                 if (rs == QF_OK) rs = run_step(plan, s, vl, theta, true, st);
@@ -2191,6 +2232,7 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
         }
         reduce_runs();
     }
+    if (rs == QF_OK) rs = cr.flush();
     std::vector<double> mhost(mcount), crhost(crcount, 0.0);
     if (rs == QF_OK && nslots > 0) {
         hipError_t e = hipMemcpyAsync(mhost.data(), mdev, mcount * sizeof(double), hipMemcpyDeviceToHost, st);
@@ -2741,12 +2783,15 @@ qf_status qf_plan_bind(qf_plan* plan, int64_t batch) {
     size_t pd = 1;
     for (const Pass& ps : plan->rev.passes)
         if (ps.tile) pd = std::max(pd, size_t(ps.nslots) * ps.geom.ntiles * size_t(batch) * E);
-    if (plan->rev.ncr > 0) pd = std::max(pd, crot_partial_doubles(uniform_view(D, plan->n, batch, plan->dtype)));
     step(dev_alloc(reinterpret_cast<void**>(&plan->w_partial), pd * sizeof(double)));
     step(dev_alloc(reinterpret_cast<void**>(&plan->w_m),
                    size_t(batch) * std::max(plan->rev.nslots, 1) * E * 2 * sizeof(double)));
     step(dev_alloc(reinterpret_cast<void**>(&plan->w_contrib), size_t(batch) * std::max(nc, 1) * sizeof(double)));
     StateView v = uniform_view(D, plan->n, batch, plan->dtype);
+    if (plan->rev.ncr > 0) {
+        plan->w_crot_cap = CrotSums::capacity(size_t(plan->rev.ncr), v);
+        step(dev_alloc(reinterpret_cast<void**>(&plan->w_crot), plan->w_crot_cap * sizeof(double)));
+    }
     step(dev_alloc(reinterpret_cast<void**>(&plan->w_expect), expect_ws_doubles(v) * sizeof(double)));
     if (rs == QF_OK && plan->seg_end.size() > 1) step(ensure_ckpt(plan, v));
     if (rs != QF_OK) {
@@ -2821,6 +2866,13 @@ qf_status qf_adjoint_grad_dev(qf_plan* plan, const qf_state* psi, const qf_state
     if (loss) QF_CHECK(launch_expect_ws(v, active, table, loss, plan->w_expect, st));
     if (!seed) QF_CHECK(launch_diag_observable(v, lam->amps, active, table_re, st));
     PassList& L = plan->rev;
+    CrotSums cr;
+    cr.buf = plan->w_crot;
+    cr.cap = plan->w_crot_cap;
+    cr.batch = v.batch;
+    cr.out = plan->w_contrib;
+    cr.ostride = uint32_t(plan->ncontrib);
+    cr.st = st;
     QF_CHECK(launch_build_mats(plan->D, plan->dtype, L.dgroups, int(L.hgroups.size()), plan->dgates, theta,
                                theta_stride, v.batch, L.dmats_b, L.nmats, st));
     const size_t sb = state_bytes(v);
@@ -2843,9 +2895,8 @@ qf_status qf_adjoint_grad_dev(qf_plan* plan, const qf_state* psi, const qf_state
                                           uint32_t(L.nslots), uint32_t(ps.slot0), st));
         } else if (ps.cr_slot >= 0) {
             const void* tab = reinterpret_cast<const unsigned char*>(L.dmats_b) + ps.mat_off * esz;
-            QF_CHECK(launch_crot_adj(v, lam->amps, crot_args(plan->gates[ps.fused.gi].op), tab, L.nmats, nullptr,
-                                     plan->w_partial, plan->w_contrib + plan->cr_contrib[size_t(ps.cr_slot)],
-                                     uint32_t(plan->ncontrib), st));
+            QF_CHECK(cr.run(v, lam->amps, crot_args(plan->gates[ps.fused.gi].op), tab, L.nmats, nullptr,
+                            plan->cr_contrib[size_t(ps.cr_slot)]));
         } else if (plan->gates[ps.fused.gi].op.kind == QF_OP_SWAP || plan->gates[ps.fused.gi].op.kind == QF_OP_MCX) {
             QF_CHECK(launch_perm_gate(v, plan->gates[ps.fused.gi].op, true, st));
             QF_CHECK(launch_perm_gate(vl, plan->gates[ps.fused.gi].op, true, st));
@@ -2855,6 +2906,7 @@ qf_status qf_adjoint_grad_dev(qf_plan* plan, const qf_state* psi, const qf_state
             QF_CHECK(launch_fused(vl, g.op.q1, g.op.q0, g.dmat_adj, st, g.real));
         }
     }
+    QF_CHECK(cr.flush());
     // seed mode: lam held torch's gradient g = 2 dL/d(conj psi), the adjoint needs dL/d(conj psi)
     return launch_grad(D, plan->dgg, int(plan->hgg.size()), plan->dgates, theta, theta_stride, plan->w_m, L.nslots,
                        v.batch, plan->w_contrib, plan->ncontrib, plan->d_poff, plan->d_plist, plan->nparams,

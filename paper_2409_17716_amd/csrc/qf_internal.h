@@ -130,12 +130,19 @@ struct CrotArgs {
 };
 qf_status launch_crot(const StateView& s, const CrotArgs& a, const void* dtab, size_t tab_stride, const double* htab,
                       hipStream_t st);
-// Un-applies the gate (inverse table) on psi and lam and writes, per register b,
-// sum over fibres of m * Im <lam_f| S |psi_f> to out[b * ostride].  partial:
-// crot_partial_doubles(s) doubles of scratch.
+// Un-applies the gate (inverse table) on psi and lam and writes crot_rows partial
+// sums per register of m * Im <lam_f| S |psi_f> to partial.
 qf_status launch_crot_adj(const StateView& s, void* lam, const CrotArgs& a, const void* dtab, size_t tab_stride,
-                          const double* htab, double* partial, double* out, uint32_t ostride, hipStream_t st);
-size_t crot_partial_doubles(const StateView& s);
+                          const double* htab, double* partial, hipStream_t st);
+uint32_t crot_rows(const StateView& s, int tgt);
+// out[b * ostride + gate.out] = the sum of gate's rows of register b, for every
+// listed gate (rows from partial + off on).
+struct CrotRows {
+    uint64_t off;
+    uint32_t rows, out;
+};
+qf_status launch_crot_reduce(const double* partial, const std::vector<CrotRows>& gates, uint32_t batch, double* out,
+                             uint32_t ostride, hipStream_t st);
 
 // ---- fused dense blocks (k_fused.hip) ----
 // real: every imaginary part of B is zero (halves the matrix-core products).
