@@ -291,13 +291,15 @@ def qf_sample(t, n: int, dim: int, shots: int, u, qudits: Optional[Sequence[int]
 def _terms_arrays(dim, terms) -> tuple:
     """terms: list of (qudit, "z") or (qudit, table of d_q complex values)."""
     qs = [int(q) for q, _ in terms]
-    tabs = []
+    tabs, clock = [], {}  # "z" diagonals of this call, one per dimension
     for q, d in terms:
         dq = _dim_of(dim, int(q))
         if isinstance(d, str):
             if d != "z":
                 raise QfError(QF_EINVAL, f"unknown term {d}")
-            tabs.append(np.exp(2j * np.pi / dq) ** np.arange(dq))
+            if dq not in clock:
+                clock[dq] = np.exp(2j * np.pi / dq) ** np.arange(dq)
+            tabs.append(clock[dq])
         else:
             tabs.append(np.asarray(d, dtype=np.complex128))
     return qs, np.concatenate(tabs)
