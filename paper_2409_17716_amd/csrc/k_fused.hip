@@ -185,8 +185,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // cycles), and fewer FP32 roundings per sum.  Error against 64 bits (relative,
 // Haar blocks on Gaussian states, also of amplitudes over many decades): K = 32
 // 5.6e-8 (FP32 matrix cores 1.5e-7), K = 49 1.1e-7 (1.8e-7), K = 128 1.9e-7
-// (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  (An infinite amplitude gives NaN where
-// a part of the block is zero.)  HBM-bound up to K = 49; time of a pass against
+// (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  The parts of an infinity, a NaN or a
+// value that rounds to infinity in bf16 do not sum to it: from a tile that holds one on,
+// a workgroup writes nothing in the loop and takes FP32 products of the amplitudes
+// themselves after it (plain_tile); the check costs nothing.  HBM-bound up to K = 49; time of a pass against
 // the FP32 cores: K = 49 on 7^9 323 -> 165 us (3.9 TB/s), K = 100 on 10^7 160 ->
 // 83 us (real 125 -> 62), K = 128 on 2^24 290 -> 110 us.
 //
@@ -219,12 +221,57 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
     }
 }
 
+// Any of the eight leading parts infinite or NaN.
+__device__ __forceinline__ bool split_overflow(const u32x4& hi) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 m = {0, 0};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, uint32_t(hi[i] & 0x7fff7fffu)));
+    return m.x >= 0x7f80 || m.y >= 0x7f80;
+}
+
 // Fibres per tile: 64 (512-byte runs of HBM), 32 for K <= 48, where more and
 // smaller workgroups do better (K = 32 on 2^24 amplitudes 54 against 70 us; K = 100
 // on 10^7 108 against 85 us).
 template <int NRB>
 constexpr int split_fibres() {
     return NRB <= 3 ? 32 : 64;
+}
+
+// One tile by FP32 products from HBM: rows row0 .. row0 + 3 of the fibres col, col +
+// 16, ...  Every lane of the workgroup calls it.
+template <int NF, bool REAL>
+__device__ __forceinline__ void plain_tile(cplx<float>* __restrict__ psi, const cplx<float>* __restrict__ B,
+                                           const FusedGeom& g, uint32_t tile, int row0, int col) {
+#pragma unroll 1
+    for (int j = 0; j < NF / 16; ++j) {
+        const uint32_t f = tile * NF + uint32_t(16 * j + col);
+        const uint32_t base = f < g.nfib ? fibre_base(g, f) : 0u;
+        f32x4 rr = {0.f, 0.f, 0.f, 0.f}, ii = rr, ri = rr;
+#pragma unroll 1
+        for (uint32_t b = 0; b < g.K; ++b) {
+            const cplx<float> x = f < g.nfib ? psi[base + b * g.L] : cmake<float>(0.f, 0.f);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t row = min(uint32_t(row0 + r), g.K - 1);
+                const cplx<float> u = B[row * g.K + b];
+                rr[r] = fmaf(u.re, x.re, rr[r]);
+                ri[r] = fmaf(u.re, x.im, ri[r]);
+                if constexpr (!REAL) {
+                    ii[r] = fmaf(u.im, x.im, ii[r]);
+                    ri[r] = fmaf(u.im, x.re, ri[r]);
+                }
+            }
+        }
+        __syncthreads();  // these fibres are read
+        if (f < g.nfib) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (uint32_t(row0 + r) < g.K)
+                    psi[base + uint32_t(row0 + r) * g.L] = cmake<float>(REAL ? rr[r] : rr[r] - ii[r], ri[r]);
+        }
+    }
 }
 
 template <int NRB, bool REAL>
@@ -238,11 +285,15 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
     constexpr int NT = 64 * NRB;
     constexpr int NU = NF * (Kp / 8);        // staging units: 8 rows of one fibre
     constexpr int UPL = (NU + NT - 1) / NT;  // per lane
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
+    // the first tile that needs FP32 products; in the padding of a fibre, since a word
+    // more of LDS made a pass of K = 49 twice as long (182 -> 363 us)
+    uint32_t& plain = *reinterpret_cast<uint32_t*>(smem + Kp * 2);
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int lr = lane & 15;  // A row / B column / C column
     const int lk = lane >> 4;  // eight k of a k block; C row group
+    if (threadIdx.x == 0) plain = ~0u;
     // the block's rows 16 wave + lr: parts of the real and imaginary entries
     u32x4 br[KB][3], bi[REAL ? 1 : KB][3];
     {
@@ -302,13 +353,17 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
             split8(v, part);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + q * PL) = part[q];
+            bool over = split_overflow(part[0]);
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = x[t][i].im;
             split8(v, part);
+            over |= split_overflow(part[0]);
+            if (over) atomicMin(&plain, tile);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + (3 + q) * PL) = part[q];
         }
         __syncthreads();
+        const uint32_t stop = plain;
         if (tile + gridDim.x < ntiles) fetch(tile + gridDim.x);
         auto mm = [](u32x4 a, u32x4 b, f32x4 c) {
             return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
@@ -340,7 +395,7 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
                 }
             }
             const uint32_t f = tile * NF + uint32_t(16 * j + lr);
-            if (f < g.nfib) {
+            if (f < g.nfib && tile < stop) {
                 const uint32_t base = fibre_base(g, f);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -350,6 +405,8 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
             }
         }
     }
+    __syncthreads();  // plain is final also where this workgroup had no tile
+    for (tile = plain; tile < ntiles; tile += gridDim.x) plain_tile<NF, REAL>(psi, B, g, tile, 16 * wave + 4 * lk, lr);
 }
 
 // The grid fills the LDS of 256 CUs once.

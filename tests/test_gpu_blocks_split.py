@@ -42,3 +42,38 @@ def test_block_parts(dims, span, real):
         err = np.abs(to_np(t).reshape(want.shape) - want)
         bound = (2 * K + 8) * 2.0 ** -24 * 2 * np.linalg.norm(x, axis=1, keepdims=True)
         assert np.all(err <= bound), (q0, K, float((err / bound).max()))
+
+
+@pytest.mark.parametrize("dims,span,q0", [([6] * 3, 2, 0), ([6] * 4, 2, 2), ([7] * 4, 2, 1), ([10] * 4, 2, 0), ([2] * 9, 7, 1)])
+@pytest.mark.parametrize("real", [False, True])
+def test_infinities_nan_and_largest_values(dims, span, q0, real):
+    """Infinite, NaN and near-overflow amplitudes (above the largest bf16 value) give what
+    FP32 products of the parts give; every other fibre, of the same tile too, is as before."""
+    import paper_2409_17716_amd as qf
+    n = len(dims)
+    K, H, L = int(np.prod(dims[q0:q0 + span])), int(np.prod(dims[:q0])), int(np.prod(dims[q0 + span:]))
+    rng = np.random.default_rng(23)
+    U = np.linalg.qr(rng.standard_normal((K, K)))[0] if real else qi.random_unitary(K, rng)
+    U = U.astype(np.complex64).astype(np.complex128)
+    x = (rng.standard_normal((H, K, L)) + 1j * rng.standard_normal((H, K, L))).astype(np.complex64)
+    odd = [complex(np.inf, 1), complex(1, -np.inf), complex(np.nan, 1), complex(3.395e38, 0)]
+    for i, v in enumerate(odd):
+        f = (i * 5) % (H * L)
+        x[f // L, :, f % L] = 0.25 if i < 3 else 0.0
+        x[f // L, (7 * i) % K, f % L] = v
+    t = to_dev(x.reshape(-1), "c64")
+    qf.Plan(dims[0], n, [("u", q0, span, U)], 0, "c64").forward(t, np.zeros(0))
+    got = to_np(t).reshape(H, K, L)
+    xr, xi = x.real.astype(np.float64), x.imag.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        wr = np.matmul(U.real, xr) - (0.0 if real else np.matmul(U.imag, xi))
+        wi = np.matmul(U.real, xi) + (0.0 if real else np.matmul(U.imag, xr))
+        norm = np.sqrt((xr ** 2 + xi ** 2).sum(axis=1, keepdims=True))
+        for g, w in ((got.real, wr), (got.imag, wi)):
+            assert np.array_equal(np.isnan(g), np.isnan(w))
+            inf = np.isinf(w)
+            assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], w[inf])
+            ok = np.isfinite(w)
+            bound = np.where(np.isfinite(norm), norm, 1.0) * (2 * K + 8) * 2.0 ** -24 * 2 + 0 * w
+            # a component that an odd entry does not reach sums the fibre's other entries
+            assert np.all(np.abs(g - w)[ok] <= np.maximum(bound, 2.0 ** -20 * K)[ok])
