@@ -915,16 +915,29 @@ qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_
                 auto fill = [&](auto& op) {
                     for (int i = 0; i < D * D; ++i) op.U.m[i] = cmake<T>(T(U[2 * i]), T(U[2 * i + 1]));
                 };
-                if (shift) {
-                    OpMatShift<T, D> op;
-                    fill(op);
-                    op.sh = *shift;
-                    op.undo = undo;
-                    return run_axis<T, D>(s, q, op, st, "one-qudit gate with a shift");
+                // Up to 12 levels the shift costs no sweep of its own (layers on 12^5
+                // 164 -> 124 us); above, D computed addresses do not fit the
+                // registers beside the fibre (16^5: 455 us) and it is one (218 us).
+                if constexpr (D <= 12) {
+                    if (shift) {
+                        OpMatShift<T, D> op;
+                        fill(op);
+                        op.sh = *shift;
+                        op.undo = undo;
+                        return run_axis<T, D>(s, q, op, st, "one-qudit gate with a shift");
+                    }
+                }
+                OpShift<T, D> mv;
+                if (shift) mv.sh = *shift;
+                if (shift && undo) {
+                    for (int i = 0; i < kMaxDim; ++i) mv.sh.shift[i] = (D - mv.sh.shift[i]) % D;
+                    if (mv.sh.mul > 0) mv.sh.mul = D - mv.sh.mul;
+                    QF_CHECK((run_axis<T, D>(s, q, mv, st, "shift of a one-qudit gate")));
                 }
                 OpMat<T, D> op;
                 fill(op);
-                return run_axis<T, D>(s, q, op, st, "qf_apply_1q");
+                QF_CHECK((run_axis<T, D>(s, q, op, st, "qf_apply_1q")));
+                return shift && !undo ? run_axis<T, D>(s, q, mv, st, "shift of a one-qudit gate") : QF_OK;
             }
         });
     });

@@ -61,3 +61,29 @@ def test_merged_shifts(c, dtype):
     ref = mixed.adjoint(c, terms)
     for b in range(2):
         assert np.all(np.abs(g[b] - ref) <= (1e-4 if dtype == "c64" else 1e-9) * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("d", [11, 12, 13, 15, 16])
+@pytest.mark.parametrize("where", [0, 1, 2])
+def test_merged_shifts_of_large_qudits(d, where):
+    """Up to 12 levels a shift goes into the sweep, above it takes one of its own:
+    CSUM, a table, X, after runs with and without angles (undone in the reverse walk)."""
+    import paper_2409_17716_amd as qf
+    dims = [3, 4]
+    dims.insert(where, d)
+    q, a, b = where, (where + 1) % 3, (where + 2) % 3
+    tab = tuple((5 * i + 2) % d for i in range(dims[a]))
+    ops = [("h", 0), ("h", 1), ("h", 2), ("csum", a, q), ("rx", q, 0, d - 1, 0), ("cshift", a, q, tab), ("h", q),
+           ("x", q, d - 2), ("cz", q, b), ("ry", q, 1, 2, 1), ("csum", b, q), ("rx", a, 0, 1, 2), ("csum", q, a)]
+    c = qi.MixedCircuit(dims, ops, np.array([0.4, -1.3, 2.1]), "large")
+    t = qf.new_state(3, dims, "c64")
+    p = qf.plan_for(c, "c64")
+    qf.qf_state_init(t, 3, dims, None)
+    p.forward(t, c.theta)
+    assert maxabs(to_np(t), mixed.run(c)) <= TOL["c64"]
+    terms = [(i, "z") for i in range(3)]
+    g = p.adjoint_grad(t, qf.new_state(3, dims, "c64"), c.theta, terms)
+    ref = mixed.adjoint(c, terms)
+    assert np.all(np.abs(g - ref) <= 1e-4 * np.abs(ref).max())
+    # the reverse walk ends at |0...0>
+    assert abs(to_np(t)[0] - 1) <= TOL["c64"]
