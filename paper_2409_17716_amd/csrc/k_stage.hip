@@ -509,15 +509,13 @@ __global__ __launch_bounds__(kSB) void k_stage_mreduce(double* __restrict__ part
     double acc = 0.0;
     if (gr < G) {
         const size_t gs = size_t(G) * step;
-        size_t i = first + size_t(gr) * step;
-        for (; i + (kU - 1) * gs < last; i += kU * gs) {
+        for (size_t i = first + size_t(gr) * step; i < last; i += kU * gs) {
             double x[kU];
 #pragma unroll
-            for (int u = 0; u < kU; ++u) x[u] = rows[(i + u * gs) * E + e];
+            for (int u = 0; u < kU; ++u) x[u] = i + u * gs < last ? rows[(i + u * gs) * E + e] : 0.0;
 #pragma unroll
             for (int u = 0; u < kU; ++u) acc += x[u];
         }
-        for (; i < last; i += gs) acc += rows[i * E + e];
     }
     red[threadIdx.x] = acc;
     __syncthreads();
@@ -619,7 +617,11 @@ __device__ __forceinline__ void r_u(cplx<T> (&v)[NV][cpow(D, M)], const cplx<T>*
 // loop over groups of kRows rows, whose matrix entries (at most 32 words) are read
 // one group ahead.  Unrolled over all rows (r_u) the compiler reads the whole
 // matrix first and spills it to vector lanes: 83 lane moves beside the 400 FMAs of
-// a real 10 x 10 U on two sub-tiles.  store(a, y): row a of every sub-tile.
+// a real 10 x 10 U on two sub-tiles.  It pays where a row's entries serve enough
+// work to cover the reads of the next rows: two sub-tiles (the complex64 adjoint,
+// 10^8 real: 81.3 -> 78.9 ms) or FP64 products (forward of 16^5 562 -> 427 us); the
+// complex64 forward keeps r_u (7^7 142 -> 127 us, 8^7 187 -> 166, real 10^7 365 ->
+// 356, real 16^5 145 -> 130).  store(a, y): row a of every sub-tile.
 template <typename T, int D, bool REAL>
 struct URows {
     static constexpr int kWords = D * (REAL ? 1 : 2) * int(sizeof(T) / 4);  // of a row
@@ -1182,7 +1184,7 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
                 });
             };
             if (kind == RK_U0) {
-                if constexpr (M == 1 && NT == 1 && URows<T, D, false>::kUse) {
+                if constexpr (M == 1 && NT == 1 && sizeof(T) == 8 && URows<T, D, false>::kUse) {
                     store_rows(std::false_type{});
                 } else {
                     r_u<T, D, M, 0, false, 1>(vv, U0);
@@ -1198,7 +1200,7 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
                 }
                 store();
             } else if (kind == RK_U0_REAL) {
-                if constexpr (M == 1 && NT == 1 && URows<T, D, true>::kUse) {
+                if constexpr (M == 1 && NT == 1 && sizeof(T) == 8 && URows<T, D, true>::kUse) {
                     store_rows(std::true_type{});
                 } else {
                     r_u<T, D, M, 0, true, 1>(vv, U0);
@@ -1937,13 +1939,15 @@ qf_status launch_stage_adj(const StateView& s, void* lam, const StageGeom& g, co
     });
 }
 
-// Rows of a chunk: up to 1024 rows are added in one launch; more in two, of about
-// the square root each, so that both levels have many short workgroups.
+// Rows of a chunk: what a workgroup reads in four turns of eight loads a lane
+// (32 * (256 / D^2) rows: 896 at D = 3, 64 at D = 10) is added in one launch; more in
+// two, of about the square root each, so that both levels have many short
+// workgroups (1000 tiles at D = 10: 25.4 us in one launch, 8.8 in two).
 qf_status launch_stage_mreduce(double* partial, uint32_t nslots, uint32_t ntiles, uint32_t batch, uint32_t D,
                                double* mout, uint32_t nslots_total, uint32_t slot0, hipStream_t st) {
     if (nslots == 0) return QF_OK;
     uint32_t step = 1;
-    if (ntiles > 1024) {
+    if (ntiles > 32 * (kSB / (D * D))) {
         while (uint64_t(step) * step < ntiles) ++step;
         hipLaunchKernelGGL(k_stage_mreduce, dim3(batch * nslots * ((ntiles + step - 1) / step)), dim3(kSB), 0, st,
                            partial, nslots, ntiles, batch, D, step, 1u, nullptr, nslots_total, slot0);

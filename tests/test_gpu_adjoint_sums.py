@@ -1,6 +1,6 @@
 """The adjoint's per-tile M sums and their reduction over the tiles: one launch up
-to 1024 tiles per register, two above (chunks of about the square root), rows of
-D^2 entries for every D, a ragged last chunk, several registers."""
+to 32 * (256 // D^2) tiles per register, two above (chunks of about the square root),
+rows of D^2 entries for every D, a ragged last chunk, several registers."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("D,n,tile", [(2, 12, 2), (2, 12, 1), (3, 8, 2), (3, 8, 1), (4, 6, 1), (5, 5, 1), (10, 4, 1),
-                                      (11, 4, 1), (16, 3, 1)])
+                                      (11, 4, 1), (16, 3, 1), (2, 13, 1), (5, 4, 1), (10, 3, 2), (16, 3, 2)])
 def test_adjoint_sums_over_many_tiles(D, n, tile):
     import paper_2409_17716_amd as qf
     c = qi.hea(D, n, 1, 5, pairs=[(0, D - 1)], clock=False)
