@@ -1394,6 +1394,17 @@ constexpr bool rounds_w8() {
     else return M == 2 ? D == 2 : (M == 1 && D >= 3 && D <= 5);
 }
 
+// The same kernel held to 4 waves per SIMD, which its 96 vector registers allow
+// 5 of at D = 16 in complex64: scheduled for 5, a complex U of 512 words takes longer
+// (forward of 16^5 194 -> 172 us, 16^4 127 -> 110; real 132 -> 135).
+template <typename T, int D, int M>
+__global__ __launch_bounds__(kSB) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_stage_rounds_w4(
+    cplx<T>* __restrict__ psi, StageGeom g, const RoundDesc* __restrict__ rounds, int nrounds,
+    const StageOp* __restrict__ ops, const cplx<T>* __restrict__ mats, size_t mat_stride,
+    const uint32_t* __restrict__ tab) {
+    stage_rounds<T, D, M>(psi, g, rounds, nrounds, ops, mats, mat_stride, tab);
+}
+
 // Pipelined persistent variant: a workgroup walks a strided sequence of
 // tiles; the global loads of the next tile are issued into
 // registers before the current tile's rounds run from LDS, so their latency
@@ -1779,6 +1790,10 @@ static qf_status launch_rounds_m(const StateView& s, const StageGeom& g, const R
     const uint32_t nthr = rounds_threads(g, cpow(D, M));
     if constexpr (rounds_w8<T, D, M>())
         hipLaunchKernelGGL((k_stage_rounds_w8<T, D, M>), dim3(grid), dim3(nthr), lds, st,
+                           reinterpret_cast<cplx<T>*>(s.amps), g, drounds, nrounds, dops,
+                           reinterpret_cast<const cplx<T>*>(dmats), mat_stride, g.tab);
+    else if constexpr (D == 16 && sizeof(T) == 4)
+        hipLaunchKernelGGL((k_stage_rounds_w4<T, D, M>), dim3(grid), dim3(nthr), lds, st,
                            reinterpret_cast<cplx<T>*>(s.amps), g, drounds, nrounds, dops,
                            reinterpret_cast<const cplx<T>*>(dmats), mat_stride, g.tab);
     else
