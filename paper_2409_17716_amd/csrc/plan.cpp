@@ -1683,8 +1683,7 @@ struct CrotSums {
     static size_t capacity(size_t ncr, const StateView& v) {
         uint32_t rows = 1;
         for (uint32_t q = 0; q < v.n; ++q) rows = std::max(rows, crot_rows(v, int(q)));
-        const size_t per = size_t(rows) * v.batch;
-        return std::max(per, std::min(per * ncr, kAdjPartial));
+        return collect_size(std::vector<size_t>(ncr, size_t(rows) * v.batch), kAdjPartial);
     }
     qf_status flush() {
         const qf_status r = launch_crot_reduce(buf, gates, batch, out, ostride, st);
@@ -1696,6 +1695,8 @@ struct CrotSums {
                   const double* htab, int slot) {
         const size_t need = size_t(crot_rows(v, a.tgt)) * v.batch;
         if (used + need > cap) QF_CHECK(flush());
+        if (need > cap)
+            return set_error(QF_ERANGE, "controlled-rotation sums: %zu values in a buffer of %zu", need, cap);
         QF_CHECK(launch_crot_adj(v, lam, a, dtab, tab_stride, htab, buf + used, st));
         gates.push_back(CrotRows{used, crot_rows(v, a.tgt), uint32_t(slot)});
         used += need;
@@ -2121,13 +2122,10 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
         for (const Pass& ps : plan->rev.passes)
             if (ps.tile) pdoubles = std::max(pdoubles, size_t(ps.nslots) * ps.geom.ntiles * v.batch * E);
     } else {
-        // the rows of all runs, within kAdjPartial
+        std::vector<size_t> needs;  // the rows of every run
         for (const Step& s : plan->steps)
-            if (s.slot >= 0) {
-                const AdjRows r = adj_axis_rows(v, s.q);
-                const size_t need = size_t(r.rows) * r.D * r.D * v.batch;
-                pdoubles = std::max(need, std::min(pdoubles + need, kAdjPartial));
-            }
+            if (s.slot >= 0) needs.push_back(adj_axis_rows(v, s.q).values(v.batch));
+        pdoubles = collect_size(needs, kAdjPartial);
     }
     const int ncr = stg ? plan->rev.ncr : plan->ncr_steps;
     CrotSums cr;
@@ -2210,8 +2208,10 @@ qf_status qf_adjoint_grad(qf_plan* plan, const qf_state* psi, const qf_state* la
                 ShiftArg sh{};
                 if (s.shift_gate >= 0) sh = step_shift(plan, s, v);
                 AdjRows r = adj_axis_rows(v, s.q);
-                const size_t need = size_t(r.rows) * r.D * r.D * v.batch;
+                const size_t need = r.values(v.batch);
                 if (used + need > pdoubles) reduce_runs();
+                if (rs == QF_OK && need > pdoubles)
+                    rs = set_error(QF_ERANGE, "adjoint partial sums: %zu values in a buffer of %zu", need, pdoubles);
                 r.off = used;
                 r.slot = uint32_t(s.slot);
                 used += need;

@@ -3,6 +3,7 @@
 // the caller.
 #pragma once
 
+#include <algorithm>
 #include <vector>
 
 #include "qf_common.h"
@@ -105,7 +106,19 @@ qf_status launch_diag_observable(const StateView& psi, void* lam_amps, const std
 struct AdjRows {
     uint64_t off;
     uint32_t rows, D, slot;
+    size_t values(uint32_t batch) const { return size_t(rows) * D * D * batch; }
 };
+// Size of the buffer that collects several gates' partial sums (needs: the values of
+// each): all of them up to limit values, at least those of the largest gate.  The
+// walk that fills it empties it first where the next gate's values do not fit.
+inline size_t collect_size(const std::vector<size_t>& needs, size_t limit) {
+    size_t sum = 0, most = 1;
+    for (size_t n : needs) {
+        sum += n;
+        most = std::max(most, n);
+    }
+    return std::max(most, std::min(sum, limit));
+}
 AdjRows adj_axis_rows(const StateView& s, int q);  // rows and D
 // W: the run's inverse; shift: a shift merged into the run, undone first; partial:
 // the run's rows.
