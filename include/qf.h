@@ -333,7 +333,11 @@ qf_status qf_plan_set_profiling(qf_plan* plan, int32_t enable);
 qf_status qf_plan_read_profile(qf_plan* plan, qf_kernel_stat* out, int32_t cap, int32_t* count);
 
 /* Apply the planned circuit in place to every register of s (shape must match
- * the plan).  theta: host, nparams angles in radians. */
+ * the plan).  theta: host, nparams angles in radians.  In a captured graph the
+ * gate matrices are copied at each replay from the plan's staging buffer, which
+ * holds those of the plan's last forward call, captured or not (no call may run
+ * while a replay is in flight); graphs that take new angles use the
+ * device-parameter mode below. */
 qf_status qf_plan_forward(qf_plan* plan, const qf_state* s, const double* theta,
                           void* stream);
 

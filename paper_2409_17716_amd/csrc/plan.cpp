@@ -1630,8 +1630,14 @@ static qf_status upload_mats(const qf_plan* p, PassList& L, const double* theta,
     const size_t esz = p->dtype == QF_C64 ? 8 : 16;
     // few matrices go by kernel argument: a launch costs the host less than a copy
     // with its event, and the staging buffer is free again at once (a forward call
-    // on 3^4, 1.2 KB: 23 -> 9 us of host time)
-    if (put_fits(L.nmats * esz)) return L.nmats ? launch_put(L.dmats, L.hmats, L.nmats * esz, st) : QF_OK;
+    // on 3^4, 1.2 KB: 23 -> 9 us of host time).  A captured call copies at any size: at
+    // a replay the matrices are those in the staging buffer, the last call's.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (put_fits(L.nmats * esz)) {
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();  // the launch reports it
+        if (cap == hipStreamCaptureStatusNone)
+            return L.nmats ? launch_put(L.dmats, L.hmats, L.nmats * esz, st) : QF_OK;
+    }
     if (L.nmats) QF_HIP_CHECK(hipMemcpyAsync(L.dmats, L.hmats, L.nmats * esz, hipMemcpyHostToDevice, st));
     QF_HIP_CHECK(hipEventRecord(L.copied, st));
     L.copied_valid = true;
