@@ -186,9 +186,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // Haar blocks on Gaussian states, also of amplitudes over many decades): K = 32
 // 5.6e-8 (FP32 matrix cores 1.5e-7), K = 49 1.1e-7 (1.8e-7), K = 128 1.9e-7
 // (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  The parts of an infinity, a NaN or a
-// value that rounds to infinity in bf16 do not sum to it: from a tile that holds one on,
-// a workgroup writes nothing in the loop and takes FP32 products of the amplitudes
-// themselves after it (plain_tile); the check costs nothing.  HBM-bound up to K = 49; time of a pass against
+// value that rounds to infinity in bf16 do not sum to it: from a tile that holds one on
+// (all tiles, where the block does), a workgroup writes nothing in the loop and takes
+// FP32 products of the amplitudes themselves after it (plain_tile); the checks cost
+// nothing.  HBM-bound up to K = 49; time of a pass against
 // the FP32 cores: K = 49 on 7^9 323 -> 165 us (3.9 TB/s), K = 100 on 10^7 160 ->
 // 83 us (real 125 -> 62), K = 128 on 2^24 290 -> 110 us.
 //
@@ -296,21 +297,30 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
     if (threadIdx.x == 0) plain = ~0u;
     // the block's rows 16 wave + lr: parts of the real and imaginary entries
     u32x4 br[KB][3], bi[REAL ? 1 : KB][3];
+    bool over = false;
     {
         const uint32_t row = uint32_t(16 * wave + lr);
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
+            // unconditional loads (of a clamped address) stay together: K = 121 on 11^6
+            // 32 us with them under their conditions, 25 us so
+            cplx<float> u[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                u[i] = B[min(row, g.K - 1) * g.K + min(uint32_t(32 * kb + 8 * lk + i), g.K - 1)];
             float xr[8], xi[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const uint32_t col = uint32_t(32 * kb + 8 * lk + i);
-                cplx<float> v = cmake<float>(0.f, 0.f);
-                if (row < g.K && col < g.K) v = B[row * g.K + col];
-                xr[i] = v.re;
-                xi[i] = v.im;
+                const bool in = row < g.K && uint32_t(32 * kb + 8 * lk + i) < g.K;
+                xr[i] = in ? u[i].re : 0.f;
+                xi[i] = in ? u[i].im : 0.f;
             }
             split8(xr, br[kb]);
-            if constexpr (!REAL) split8(xi, bi[kb]);
+            over |= split_overflow(br[kb][0]);
+            if constexpr (!REAL) {
+                split8(xi, bi[kb]);
+                over |= split_overflow(bi[kb][0]);
+            }
         }
     }
     const uint32_t ntiles = (g.nfib + NF - 1) / NF;
@@ -353,15 +363,15 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
             split8(v, part);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + q * PL) = part[q];
-            bool over = split_overflow(part[0]);
+            over |= split_overflow(part[0]);
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = x[t][i].im;
             split8(v, part);
             over |= split_overflow(part[0]);
-            if (over) atomicMin(&plain, tile);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + (3 + q) * PL) = part[q];
         }
+        if (over) atomicMin(&plain, tile);
         __syncthreads();
         const uint32_t stop = plain;
         if (tile + gridDim.x < ntiles) fetch(tile + gridDim.x);

@@ -1,0 +1,58 @@
+"""Dense blocks of 32 <= K <= 128 in complex64 (bf16 matrix cores on three-part
+operands): blocks with entries that have no such parts, amplitudes and entries near the
+smallest numbers, and the precision of the products."""
+import numpy as np
+import pytest
+
+import qf_inputs as qi
+from tests.gpu_helpers import to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [([2] * 8, 5, 1), ([6] * 4, 2, 0), ([7] * 4, 2, 2), ([10] * 4, 2, 1), ([2] * 9, 7, 0)]
+
+
+def _split(dims, span, q0):
+    return int(np.prod(dims[:q0])), int(np.prod(dims[q0:q0 + span])), int(np.prod(dims[q0 + span:]))
+
+
+def _parts(U, x, real):
+    """Real and imaginary parts of U x, the real products summed by themselves."""
+    xr, xi = x.real.astype(np.float64), x.imag.astype(np.float64)
+    wr = np.matmul(U.real, xr) - (0.0 if real else np.matmul(U.imag, xi))
+    wi = np.matmul(U.real, xi) + (0.0 if real else np.matmul(U.imag, xr))
+    return wr, wi
+
+
+def _apply(dims, span, q0, U, x):
+    import paper_2409_17716_amd as qf
+    t = to_dev(x.reshape(-1), "c64")
+    qf.qf_apply_fused(t, len(dims), dims[0], q0, span, to_dev(U.reshape(-1), "c64"))
+    return to_np(t).reshape(x.shape)
+
+
+@pytest.mark.parametrize("dims,span,q0", SHAPES)
+def test_block_entries_without_parts(dims, span, q0):
+    """Infinite, NaN, and largest entries (above the largest bf16 value, and below it at a
+    size whose sums could leave FP32 where the result does not): what FP32 products give."""
+    H, K, L = _split(dims, span, q0)
+    rng = np.random.default_rng(41)
+    x = (rng.standard_normal((H, K, L)) + 1j * rng.standard_normal((H, K, L))).astype(np.complex64) * 0.01
+    for v in (complex(np.inf, 0.5), complex(0.5, -np.inf), complex(np.nan, 1), 3.395e38, complex(0, -3.395e38), 2e38,
+              1e30):
+        U = qi.random_unitary(K, rng).astype(np.complex64)
+        U[K // 3] = 0.25
+        U[K // 3, K - 1] = v
+        got = _apply(dims, span, q0, U, x)
+        with np.errstate(invalid="ignore"):
+            want = _parts(U.astype(np.complex128), x, False)
+            for g, w in zip((got.real, got.imag), want):
+                assert np.array_equal(np.isnan(g), np.isnan(w)), v
+                inf = np.isinf(w)
+                assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], w[inf]), v
+                ok = np.isfinite(w)
+                # a sum of 2 K products, each partial sum rounded by 2^-24 of at most the
+                # row's largest magnitudes times the fibre's
+                size = np.where(np.isfinite(U), np.abs(U).astype(np.float64), 0).max(axis=1)[None, :, None] * \
+                    np.abs(x).astype(np.float64).sum(axis=1, keepdims=True) * np.ones(w.shape)
+                assert np.all((np.abs(g - w) <= 4 * K * 2.0 ** -24 * size)[ok]), v
