@@ -185,9 +185,12 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // cycles), and fewer FP32 roundings per sum.  Error against 64 bits (relative,
 // Haar blocks on Gaussian states, also of amplitudes over many decades): K = 32
 // 5.6e-8 (FP32 matrix cores 1.5e-7), K = 49 1.1e-7 (1.8e-7), K = 128 1.9e-7
-// (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  The parts of an infinity, a NaN or a
-// value that rounds to infinity in bf16 do not sum to it: from a tile that holds one on
-// (all tiles, where the block does), a workgroup writes nothing in the loop and takes
+// (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  Both factors are multiplied by 2^23 first,
+// so that the parts of the smallest subnormal are normal bf16 values (the matrix core
+// takes subnormal ones for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none), and
+// the results by 2^-46.  Entries of 2^25 and more and amplitudes of 2^48 and more, whose
+// scaled sums could overflow, infinities and NaN: from a tile that holds one on (all
+// tiles, where the block does), a workgroup writes nothing in the loop and takes
 // FP32 products of the amplitudes themselves after it (plain_tile); the checks cost
 // nothing.  HBM-bound up to K = 49; time of a pass against
 // the FP32 cores: K = 49 on 7^9 323 -> 165 us (3.9 TB/s), K = 100 on 10^7 160 ->
@@ -222,14 +225,21 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
     }
 }
 
-// Any of the eight leading parts infinite or NaN.
-__device__ __forceinline__ bool split_overflow(const u32x4& hi) {
+// Scale of the factors, and log2 of the scaled amplitudes' and entries' limits: 128
+// products of each kind add up to less than 2^(7 + 71 + 48 + 1).
+constexpr float kSplitScale = 0x1p23f, kSplitBack = 0x1p-46f;
+constexpr int kSplitX = 48 + 23, kSplitB = 25 + 23;
+
+// Any of the eight leading parts at or above 2^E, infinite or NaN.
+template <int E>
+__device__ __forceinline__ bool split_over(const u32x4& hi) {
     typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
     u16x2 m = {0, 0};
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, uint32_t(hi[i] & 0x7fff7fffu)));
-    return m.x >= 0x7f80 || m.y >= 0x7f80;
+    constexpr uint16_t lim = uint16_t((E + 127) << 7);
+    return m.x >= lim || m.y >= lim;
 }
 
 // Fibres per tile: 64 (512-byte runs of HBM), 32 for K <= 48, where more and
@@ -312,14 +322,14 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const bool in = row < g.K && uint32_t(32 * kb + 8 * lk + i) < g.K;
-                xr[i] = in ? u[i].re : 0.f;
-                xi[i] = in ? u[i].im : 0.f;
+                xr[i] = in ? u[i].re * kSplitScale : 0.f;
+                xi[i] = in ? u[i].im * kSplitScale : 0.f;
             }
             split8(xr, br[kb]);
-            over |= split_overflow(br[kb][0]);
+            over |= split_over<kSplitB>(br[kb][0]);
             if constexpr (!REAL) {
                 split8(xi, bi[kb]);
-                over |= split_overflow(bi[kb][0]);
+                over |= split_over<kSplitB>(bi[kb][0]);
             }
         }
     }
@@ -359,15 +369,15 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
             u32x4 part[3];
             unsigned char* p = smem + f * CS + k8 * 16;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = x[t][i].re;
+            for (int i = 0; i < 8; ++i) v[i] = x[t][i].re * kSplitScale;
             split8(v, part);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + q * PL) = part[q];
-            over |= split_overflow(part[0]);
+            over |= split_over<kSplitX>(part[0]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = x[t][i].im;
+            for (int i = 0; i < 8; ++i) v[i] = x[t][i].im * kSplitScale;
             split8(v, part);
-            over |= split_overflow(part[0]);
+            over |= split_over<kSplitX>(part[0]);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + (3 + q) * PL) = part[q];
         }
@@ -410,7 +420,9 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const uint32_t row = uint32_t(16 * wave + 4 * lk + r);
-                    if (row < g.K) psi[base + row * g.L] = cmake<float>(REAL ? rr[r] : rr[r] - ii[r], ri[r]);
+                    if (row < g.K)
+                        psi[base + row * g.L] =
+                            cmake<float>((REAL ? rr[r] : rr[r] - ii[r]) * kSplitBack, ri[r] * kSplitBack);
                 }
             }
         }

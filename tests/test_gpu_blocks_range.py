@@ -56,3 +56,22 @@ def test_block_entries_without_parts(dims, span, q0):
                 size = np.where(np.isfinite(U), np.abs(U).astype(np.float64), 0).max(axis=1)[None, :, None] * \
                     np.abs(x).astype(np.float64).sum(axis=1, keepdims=True) * np.ones(w.shape)
                 assert np.all((np.abs(g - w) <= 4 * K * 2.0 ** -24 * size)[ok]), v
+
+
+@pytest.mark.parametrize("dims,span,q0", SHAPES)
+@pytest.mark.parametrize("ex,eb", [(-100, 0), (-117, 0), (-122, 0), (-60, -60), (0, -117), (20, 20), (47, 0),
+                                   (50, 0), (0, 26)])
+def test_scales(dims, span, q0, ex, eb):
+    """Amplitudes about 2^ex and a block of 2^eb times a unitary: results keep FP32's
+    relative precision as long as they are normal numbers themselves (each of the fibre's
+    amplitudes and the block's entries is taken whole, a result rounds once more)."""
+    H, K, L = _split(dims, span, q0)
+    rng = np.random.default_rng(43)
+    x = ((rng.standard_normal((H, K, L)) + 1j * rng.standard_normal((H, K, L))) * 2.0 ** ex).astype(np.complex64)
+    U = (qi.random_unitary(K, rng) * 2.0 ** eb).astype(np.complex64)
+    got = _apply(dims, span, q0, U, x)
+    wr, wi = _parts(U.astype(np.complex128), x, False)
+    err = np.sqrt(np.mean((got.real - wr) ** 2 + (got.imag - wi) ** 2) / np.mean(wr ** 2 + wi ** 2))
+    # K / 4 to 2 K additions in FP32, each rounding by at most 2^-24 of a partial sum,
+    # independently: sqrt(2 K / 3) 2^-24
+    assert err <= np.sqrt(2 * K / 3) * 2.0 ** -24, (err, ex, eb)
