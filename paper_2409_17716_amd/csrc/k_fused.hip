@@ -182,10 +182,14 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // products above 2^-26 of it (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid),
 // exact in the matrix core and added in FP32: 24 v_mfma_f32_16x16x32_bf16 (16
 // cycles each) per 32 complex rows in place of 32 v_mfma_f32_16x16x4f32 (32
-// cycles), and fewer FP32 roundings per sum.  Error against 64 bits (relative,
-// Haar blocks on Gaussian states, also of amplitudes over many decades): K = 32
-// 5.6e-8 (FP32 matrix cores 1.5e-7), K = 49 1.1e-7 (1.8e-7), K = 128 1.9e-7
-// (2.9e-7), K = 100 real 1.4e-7 (1.8e-7).  Both factors are multiplied by 2^23 first,
+// cycles).  The products hi hi have an accumulator of their own: the others, 2^-8 of
+// them, are summed without the rounding of the large sum, which is one addition for
+// 32 rows.  Where a row's largest entry is at least 2/5 of its sum, so that a result
+// can be one product with the one rounding of an FP32 product, two more are kept
+// (mid lo, lo mid).  Relative error against 64 bits (rms; FP32 matrix cores, then
+// these), Haar blocks on Gaussian states: K = 32 1.5e-7, 4.8e-8; K = 49 1.8e-7,
+// 5.6e-8; K = 128 2.9e-7, 8.1e-8; K = 100 real 1.8e-7, 6.0e-8; diagonal phases 3.1e-8,
+// 2.6e-8; real diagonals 2.5e-8, 2.5e-8; permutations exact.  Both factors are multiplied by 2^23 first,
 // so that the parts of the smallest subnormal are normal bf16 values (the matrix core
 // takes subnormal ones for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none), and
 // the results by 2^-46.  Entries of 2^25 and more and amplitudes of 2^48 and more, whose
@@ -193,8 +197,8 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // tiles, where the block does), a workgroup writes nothing in the loop and takes
 // FP32 products of the amplitudes themselves after it (plain_tile); the checks cost
 // nothing.  HBM-bound up to K = 49; time of a pass against
-// the FP32 cores: K = 49 on 7^9 323 -> 165 us (3.9 TB/s), K = 100 on 10^7 160 ->
-// 83 us (real 125 -> 62), K = 128 on 2^24 290 -> 110 us.
+// the FP32 cores: K = 36 on 6^8 26 -> 22 us, K = 49 on 7^9 317 -> 190 us, K = 100 on
+// 10^7 158 -> 87 us (real 125 -> 62), K = 128 on 2^24 280 -> 114 us.
 //
 // A persistent workgroup of NRB wavefronts owns one row block of 16 per wavefront,
 // its block's operands in registers.  A tile of NF fibres lies in LDS as
@@ -285,8 +289,15 @@ __device__ __forceinline__ void plain_tile(cplx<float>* __restrict__ psi, const 
     }
 }
 
+// Wavefronts per SIMD the registers are held to: K <= 64 takes 3 (complex; 36 on 6^8
+// 25 us with 2 of them, 22 with 3), other sizes what the compiler finds.
+template <int NRB>
+constexpr unsigned split_waves() {
+    return NRB == 3 || NRB == 4 ? 3 : (NRB + 3) / 4;
+}
+
 template <int NRB, bool REAL>
-__global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restrict__ psi,
+__global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_waves<NRB>()))) void k_fused_split(cplx<float>* __restrict__ psi,
                                                           const cplx<float>* __restrict__ B, FusedGeom g) {
     constexpr int KB = (NRB + 1) / 2;        // k blocks of 32
     constexpr int Kp = 32 * KB;
@@ -308,6 +319,7 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
     // the block's rows 16 wave + lr: parts of the real and imaginary entries
     u32x4 br[KB][3], bi[REAL ? 1 : KB][3];
     bool over = false;
+    float largest = 0.f, sum = 0.f;  // of the row's entries
     {
         const uint32_t row = uint32_t(16 * wave + lr);
 #pragma unroll
@@ -324,6 +336,9 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
                 const bool in = row < g.K && uint32_t(32 * kb + 8 * lk + i) < g.K;
                 xr[i] = in ? u[i].re * kSplitScale : 0.f;
                 xi[i] = in ? u[i].im * kSplitScale : 0.f;
+                const float m = fabsf(xr[i]) + fabsf(xi[i]);
+                largest = fmaxf(largest, m);
+                sum += m;
             }
             split8(xr, br[kb]);
             over |= split_over<kSplitB>(br[kb][0]);
@@ -333,6 +348,12 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
             }
         }
     }
+#pragma unroll
+    for (int m = 16; m < 64; m <<= 1) {
+        largest = fmaxf(largest, __shfl_xor(largest, m, 64));
+        sum += __shfl_xor(sum, m, 64);
+    }
+    const bool dominated = __any(largest > 0.f && sum <= 2.5f * largest);
     const uint32_t ntiles = (g.nfib + NF - 1) / NF;
     cplx<float> x[UPL][8];
     // unit u: fibre u % NF, rows 8 (u / NF) .. + 7 (consecutive lanes: consecutive
@@ -389,40 +410,51 @@ __global__ __launch_bounds__(64 * NRB) void k_fused_split(cplx<float>* __restric
             return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
                                                            c, 0, 0, 0);
         };
-#pragma unroll
+#pragma unroll 1
         for (int j = 0; j < NF / 16; ++j) {
-            // B_re X_re, B_im X_im, B_re X_im + B_im X_re
-            f32x4 rr = {0.f, 0.f, 0.f, 0.f}, ii = rr, ri = rr;
+            // B_re X_re, B_im X_im, B_re X_im + B_im X_re: [0] the products of the
+            // leading parts, [1] the others
+            f32x4 rr[2] = {}, ii[2] = {}, ri[2] = {};
             const unsigned char* p = smem + (16 * j + lr) * CS + lk * 16;
+            auto part = [&](int q, int kb) { return *reinterpret_cast<const u32x4*>(p + q * PL + kb * 64); };
+            auto product = [&](int s, u32x4 ar, u32x4 ai, u32x4 xr, u32x4 xi) {
+                rr[s] = mm(ar, xr, rr[s]);
+                ri[s] = mm(ar, xi, ri[s]);
+                if constexpr (!REAL) {
+                    ii[s] = mm(ai, xi, ii[s]);
+                    ri[s] = mm(ai, xr, ri[s]);
+                }
+            };
+            if (dominated) {  // mid lo, lo mid
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) {
+                    product(1, br[kb][1], bi[REAL ? 0 : kb][1], part(2, kb), part(5, kb));
+                    product(1, br[kb][2], bi[REAL ? 0 : kb][2], part(1, kb), part(4, kb));
+                }
+            }
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 u32x4 xr[3], xi[3];
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
-                    xr[q] = *reinterpret_cast<const u32x4*>(p + q * PL + kb * 64);
-                    xi[q] = *reinterpret_cast<const u32x4*>(p + (3 + q) * PL + kb * 64);
+                    xr[q] = part(q, kb);
+                    xi[q] = part(3 + q, kb);
                 }
                 // smallest partial products first
                 constexpr int pa[6] = {1, 2, 0, 1, 0, 0}, pb[6] = {1, 0, 2, 0, 1, 0};
 #pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    rr = mm(br[kb][pa[q]], xr[pb[q]], rr);
-                    ri = mm(br[kb][pa[q]], xi[pb[q]], ri);
-                    if constexpr (!REAL) {
-                        ii = mm(bi[kb][pa[q]], xi[pb[q]], ii);
-                        ri = mm(bi[kb][pa[q]], xr[pb[q]], ri);
-                    }
-                }
+                for (int q = 0; q < 6; ++q)
+                    product(q < 5, br[kb][pa[q]], bi[REAL ? 0 : kb][pa[q]], xr[pb[q]], xi[pb[q]]);
             }
+            rr[0] = REAL ? rr[0] + rr[1] : (rr[0] - ii[0]) + (rr[1] - ii[1]);
+            ri[0] = ri[0] + ri[1];
             const uint32_t f = tile * NF + uint32_t(16 * j + lr);
             if (f < g.nfib && tile < stop) {
                 const uint32_t base = fibre_base(g, f);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const uint32_t row = uint32_t(16 * wave + 4 * lk + r);
-                    if (row < g.K)
-                        psi[base + row * g.L] =
-                            cmake<float>((REAL ? rr[r] : rr[r] - ii[r]) * kSplitBack, ri[r] * kSplitBack);
+                    if (row < g.K) psi[base + row * g.L] = cmake<float>(rr[0][r] * kSplitBack, ri[0][r] * kSplitBack);
                 }
             }
         }

@@ -75,3 +75,50 @@ def test_scales(dims, span, q0, ex, eb):
     # K / 4 to 2 K additions in FP32, each rounding by at most 2^-24 of a partial sum,
     # independently: sqrt(2 K / 3) 2^-24
     assert err <= np.sqrt(2 * K / 3) * 2.0 ** -24, (err, ex, eb)
+
+
+def _fp32(U, x):
+    """U x for one entry per row, each part by FP32 products and one FP32 addition."""
+    K = U.shape[0]
+    col = np.abs(U).argmax(axis=1)
+    u = U[np.arange(K), col][None, :, None]
+    v = x[:, col, :]
+    re = (u.real * v.real) - (u.imag * v.imag)
+    im = (u.real * v.imag) + (u.imag * v.real)
+    assert re.dtype == np.float32
+    return re, im
+
+
+@pytest.mark.parametrize("dims,span,q0", [([2] * 14, 5, 4), ([6] * 6, 2, 1), ([7] * 5, 2, 2), ([10] * 4, 2, 1),
+                                          ([2] * 14, 7, 0)])
+@pytest.mark.parametrize("real", [False, True])
+def test_precision_of_the_products(dims, span, q0, real):
+    import paper_2409_17716_amd as qf
+    H, K, L = _split(dims, span, q0)
+    rng = np.random.default_rng(47)
+    x = (rng.standard_normal((H, K, L)) + 1j * rng.standard_normal((H, K, L))).astype(np.complex64)
+
+    def run(U):
+        t = to_dev(x.reshape(-1), "c64")
+        qf.Plan(dims[0], len(dims), [("u", q0, span, U.astype(np.complex128))], 0, "c64").forward(t, np.zeros(0))
+        return to_np(t).reshape(x.shape)
+
+    def rms(g, U):
+        w = np.matmul(U.astype(np.complex128), x.astype(np.complex128))
+        return np.sqrt(np.mean(np.abs(g - w) ** 2) / np.mean(np.abs(w) ** 2))
+    # a dense block: the sum of the leading parts' products rounds once for 32 rows (2^-24
+    # of a partial sum at most), the two additions that join the sums round by 2^-25; with
+    # the low parts' products left out the error is 1e-6 and more
+    U = np.linalg.qr(rng.standard_normal((K, K)))[0].astype(np.complex64) if real else \
+        qi.random_unitary(K, rng).astype(np.complex64)
+    assert rms(run(U), U) <= (1 + (K + 31) // 32 / 2) * 2.0 ** -24
+    # a permutation moves the amplitudes: hi + mid + lo is the amplitude itself
+    perm = rng.permutation(K)
+    P = np.eye(K)[perm].astype(np.complex64)
+    assert np.array_equal(run(P), x[:, perm, :].astype(np.complex128))
+    # one entry per row: no further off than FP32 products and their sum (the two errors
+    # are means over at least 10^4 results, known to about 1%)
+    d = rng.standard_normal(K) if real else np.exp(2j * np.pi * rng.random(K))
+    D = (np.eye(K)[perm] * d).astype(np.complex64)
+    re, im = _fp32(D, x)
+    assert rms(run(D), D) <= 1.02 * rms(re.astype(np.float64) + 1j * im, D)
