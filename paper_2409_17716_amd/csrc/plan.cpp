@@ -253,15 +253,15 @@ struct PassList {
     std::vector<StageOp> hops;
     std::vector<RoundDesc> hrounds;
     RoundDesc* drounds = nullptr;
-    std::vector<uint32_t> htab;      // geometry tables of the passes in register rounds
-    uint32_t* dtab = nullptr;
+    std::vector<uint32_t> htab;      // geometry tables of the passes in register rounds, one per tile
     std::vector<DevGroup> hgroups;   // bound mode: matrices built on the device
     DevGroup* dgroups = nullptr;
     void* dmats_b = nullptr;         // bound mode: batch x nmats matrices
     size_t nmats = 0;
     int nslots = 0;
     int ncr = 0;                     // controlled-rotation passes
-    StageOp* dops = nullptr;
+    void* dlist = nullptr;           // device: ops, rounds, tables and matrices
+    StageOp* dops = nullptr;         // (parts of dlist)
     void* dmats = nullptr;
     void* hmats = nullptr;
     hipEvent_t copied = nullptr, done = nullptr;
@@ -274,17 +274,13 @@ struct PassList {
     }
     void release() {
         release_bound();
-        if (drounds) (void)hipFree(drounds);
-        drounds = nullptr;
-        if (dtab) (void)hipFree(dtab);
-        dtab = nullptr;
-        if (dops) (void)hipFree(dops);
-        if (dmats) (void)hipFree(dmats);
+        if (dlist) (void)hipFree(dlist);
         if (hmats) (void)hipHostFree(hmats);
         if (copied) (void)hipEventDestroy(copied);
         if (done) (void)hipEventDestroy(done);
         dops = nullptr;
-        dmats = hmats = nullptr;
+        drounds = nullptr;
+        dlist = dmats = hmats = nullptr;
         copied = done = nullptr;
     }
 };
@@ -1422,6 +1418,7 @@ static void finalize_passes(const qf_plan* p, PassList& L, bool adjoint) {
     L.nmats = 0;
     L.nslots = 0;
     L.ncr = 0;
+    std::vector<uint32_t> tab;
     const int ng = int(p->gates.size());
     for (Pass& ps : L.passes) {
         if (!ps.tile) {
@@ -1500,41 +1497,67 @@ static void finalize_passes(const qf_plan* p, PassList& L, bool adjoint) {
         ps.nops = int(ps.ops.size());
         build_rounds(p, ps, L, dim_of, moff, adjoint);
         if (ps.nrounds > 0) {
-            std::vector<uint32_t> tab;
-            stage_table(uint32_t(D), adjoint ? adj_group(p) : p->group, ps.geom, tab);
+            // passes over the same tile qudits share a table (a deep circuit has few tiles)
+            const Pass* same = nullptr;
+            for (const Pass& o : L.passes) {
+                if (&o == &ps) break;
+                if (o.tile && o.nrounds > 0 && o.T == ps.T) {
+                    same = &o;
+                    break;
+                }
+            }
+            if (same) {
+                ps.geom = same->geom;
+                ps.tab_off = same->tab_off;
+            } else {
+                stage_table(uint32_t(D), adjoint ? adj_group(p) : p->group, ps.geom, tab);
+                ps.tab_off = L.htab.size();
+                L.htab.insert(L.htab.end(), tab.begin(), tab.end());
+            }
             ps.geom.use_offhi = ps.geom.io_lanes == 0;
             for (int i = 0; i < ps.nrounds; ++i)
                 if (L.hrounds[size_t(ps.round_off + i)].need_gidx) ps.geom.use_offhi = 1;
-            ps.tab_off = L.htab.size();
-            L.htab.insert(L.htab.end(), tab.begin(), tab.end());
         }
         ps.nmat = moff;
         L.nmats += moff;
     }
 }
 
+// Device copies of a list's ops, rounds and tables, and room for its matrices: one
+// allocation and one copy (with one each, a fresh plan's first forward on 3^7 took 11 us
+// longer than with ops and rounds alone).
 static qf_status upload_ops(const qf_plan* p, PassList& L) {
     const size_t esz = p->dtype == QF_C64 ? 8 : 16;
-    if (!L.hops.empty()) {
-        QF_CHECK(dev_malloc(reinterpret_cast<void**>(&L.dops), L.hops.size() * sizeof(StageOp), "stage ops"));
-        QF_HIP_CHECK(hipMemcpy(L.dops, L.hops.data(), L.hops.size() * sizeof(StageOp), hipMemcpyHostToDevice));
-    }
-    if (!L.hrounds.empty()) {
-        QF_CHECK(dev_malloc(reinterpret_cast<void**>(&L.drounds), L.hrounds.size() * sizeof(RoundDesc), "rounds"));
-        QF_HIP_CHECK(hipMemcpy(L.drounds, L.hrounds.data(), L.hrounds.size() * sizeof(RoundDesc),
-                               hipMemcpyHostToDevice));
-    }
-    if (!L.htab.empty()) {
-        QF_CHECK(dev_malloc(reinterpret_cast<void**>(&L.dtab), L.htab.size() * sizeof(uint32_t), "stage tables"));
-        QF_HIP_CHECK(hipMemcpy(L.dtab, L.htab.data(), L.htab.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        for (Pass& ps : L.passes)
-            if (ps.tile && ps.nrounds > 0) ps.geom.tab = L.dtab + ps.tab_off;
-    }
     const size_t mb = std::max<size_t>(L.nmats, 1) * esz;
-    QF_CHECK(dev_malloc(&L.dmats, mb, "stage matrices"));
-    QF_CHECK(host_malloc_pinned(&L.hmats, mb, "stage matrix staging"));
-    QF_HIP_CHECK(hipEventCreateWithFlags(&L.copied, hipEventDisableTiming));
-    QF_HIP_CHECK(hipEventCreateWithFlags(&L.done, hipEventDisableTiming));
+    size_t bytes = 0;
+    auto place = [&](size_t n) {
+        const size_t at = bytes;
+        bytes = (bytes + n + 255) & ~size_t(255);
+        return at;
+    };
+    const size_t ops = place(L.hops.size() * sizeof(StageOp));
+    const size_t rounds = place(L.hrounds.size() * sizeof(RoundDesc));
+    const size_t tab = place(L.htab.size() * sizeof(uint32_t));
+    const size_t fixed = bytes;
+    const size_t mats = place(mb);
+    std::vector<unsigned char> h(fixed);
+    auto put = [&](size_t at, const void* src, size_t n) {
+        if (n) std::memcpy(h.data() + at, src, n);
+    };
+    put(ops, L.hops.data(), L.hops.size() * sizeof(StageOp));
+    put(rounds, L.hrounds.data(), L.hrounds.size() * sizeof(RoundDesc));
+    put(tab, L.htab.data(), L.htab.size() * sizeof(uint32_t));
+    if (!L.dlist) QF_CHECK(dev_malloc(&L.dlist, bytes, "stage ops and matrices"));
+    if (!L.hmats) QF_CHECK(host_malloc_pinned(&L.hmats, mb, "stage matrix staging"));
+    if (!L.copied) QF_HIP_CHECK(hipEventCreateWithFlags(&L.copied, hipEventDisableTiming));
+    if (!L.done) QF_HIP_CHECK(hipEventCreateWithFlags(&L.done, hipEventDisableTiming));
+    if (fixed) QF_HIP_CHECK(hipMemcpy(L.dlist, h.data(), fixed, hipMemcpyHostToDevice));
+    unsigned char* d = reinterpret_cast<unsigned char*>(L.dlist);
+    L.dops = reinterpret_cast<StageOp*>(d + ops);
+    L.drounds = reinterpret_cast<RoundDesc*>(d + rounds);
+    for (Pass& ps : L.passes)
+        if (ps.tile && ps.nrounds > 0) ps.geom.tab = reinterpret_cast<uint32_t*>(d + tab) + ps.tab_off;
+    L.dmats = d + mats;
     return QF_OK;
 }
 
