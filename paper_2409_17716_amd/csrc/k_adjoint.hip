@@ -125,43 +125,54 @@ __global__ __launch_bounds__(kFB) void k_adj_axis(cplx<T>* __restrict__ psi, cpl
     }
 }
 
-// The rows of up to kAdjRows runs, each summed by one workgroup per register in a
-// fixed order (lane = entry of one of 256 / E rows at a time, eight rows in flight)
-// and written as the complex anti-Hermitian matrix.
+// The rows of up to kAdjRows runs, summed in a fixed order (lane = entry of one of
+// 256 / E rows at a time, eight rows in flight) by one workgroup per run and register
+// and written as the complex anti-Hermitian matrix.  Runs of more rows than a workgroup
+// reads in four turns (AdjRows::chunk) are first summed by chunks (CHUNKS: blockIdx.y),
+// each chunk's sum replacing its first row, which no other workgroup reads.
 constexpr int kAdjRows = 64;
 
 struct AdjRowsArg {
     AdjRows run[kAdjRows];
 };
 
-__global__ __launch_bounds__(256) void k_adj_reduce(const double* __restrict__ partial, AdjRowsArg a, uint32_t batch,
+template <bool CHUNKS>
+__global__ __launch_bounds__(256) void k_adj_reduce(double* __restrict__ partial, AdjRowsArg a, uint32_t batch,
                                                     uint32_t nslots, uint32_t slot_elems, double* __restrict__ out) {
     __shared__ double red[256];
     __shared__ double sum[256];
     const uint32_t r = blockIdx.x / batch, b = blockIdx.x - r * batch;
-    const uint32_t D = a.run[r].D, rows = a.run[r].rows, E = D * D;
-    const double* p = partial + a.run[r].off + size_t(b) * rows * E;
+    const uint32_t D = a.run[r].D, rows = a.run[r].rows, chunk = a.run[r].chunk, E = D * D;
+    const uint32_t first = CHUNKS ? blockIdx.y * chunk : 0u;
+    if (CHUNKS && (chunk == rows || first >= rows)) return;
+    const uint32_t last = CHUNKS ? min(rows, first + chunk) : rows;
+    const uint32_t step = CHUNKS || chunk == rows ? 1u : chunk;
+    double* p = partial + a.run[r].off + size_t(b) * rows * E;
     const uint32_t G = 256 / E, gr = threadIdx.x / E, e = threadIdx.x - gr * E;
     constexpr uint32_t kU = 8;
     double acc = 0.0;
     if (gr < G) {
-        uint32_t i = gr;
-        for (; i + (kU - 1) * G < rows; i += kU * G) {
+        uint32_t i = first + gr * step;
+        for (; i + (kU - 1) * G * step < last; i += kU * G * step) {
             double x[kU];
 #pragma unroll
-            for (uint32_t u = 0; u < kU; ++u) x[u] = p[size_t(i + u * G) * E + e];
+            for (uint32_t u = 0; u < kU; ++u) x[u] = p[size_t(i + u * G * step) * E + e];
 #pragma unroll
             for (uint32_t u = 0; u < kU; ++u) acc += x[u];
         }
-        for (; i < rows; i += G) acc += p[size_t(i) * E + e];
+        for (; i < last; i += G * step) acc += p[size_t(i) * E + e];
     }
     red[threadIdx.x] = acc;
     __syncthreads();
     if (threadIdx.x < E) {
         double t = 0.0;
         for (uint32_t q = 0; q < G; ++q) t += red[q * E + threadIdx.x];
-        sum[threadIdx.x] = t;
+        if (CHUNKS)
+            p[size_t(first) * E + threadIdx.x] = t;
+        else
+            sum[threadIdx.x] = t;
     }
+    if (CHUNKS) return;
     __syncthreads();
     if (threadIdx.x < E) {
         const uint32_t x = threadIdx.x / D, y = threadIdx.x - x * D;
@@ -203,6 +214,10 @@ AdjRows adj_axis_rows(const StateView& s, int q) {
     AdjRows r{};
     r.D = s.dims[q];
     r.rows = adj_axis_wgs((s.N / r.D + kFB - 1) / kFB);
+    // more than four turns of a workgroup: chunks of the square root
+    r.chunk = r.rows;
+    if (r.rows > 32 * (256 / (r.D * r.D)))
+        for (r.chunk = 1; r.chunk * r.chunk < r.rows;) ++r.chunk;
     return r;
 }
 
@@ -232,14 +247,23 @@ qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W,
     });
 }
 
-qf_status launch_adj_reduce(const double* partial, const std::vector<AdjRows>& runs, uint32_t batch, double* mout,
+qf_status launch_adj_reduce(double* partial, const std::vector<AdjRows>& runs, uint32_t batch, double* mout,
                             uint32_t nslots, uint32_t slot_elems, hipStream_t st) {
     for (size_t i = 0; i < runs.size(); i += kAdjRows) {
         const size_t n = std::min(runs.size() - i, size_t(kAdjRows));
         AdjRowsArg a{};
-        for (size_t j = 0; j < n; ++j) a.run[j] = runs[i + j];
-        hipLaunchKernelGGL(k_adj_reduce, dim3(uint32_t(n) * batch), dim3(256), 0, st, partial, a, batch, nslots,
-                           slot_elems, mout);
+        uint32_t chunks = 1;
+        for (size_t j = 0; j < n; ++j) {
+            a.run[j] = runs[i + j];
+            chunks = std::max(chunks, (a.run[j].rows + a.run[j].chunk - 1) / a.run[j].chunk);
+        }
+        if (chunks > 1) {
+            hipLaunchKernelGGL(k_adj_reduce<true>, dim3(uint32_t(n) * batch, chunks), dim3(256), 0, st, partial, a,
+                               batch, nslots, slot_elems, mout);
+            QF_CHECK(check_launch("adjoint reduce (chunks)"));
+        }
+        hipLaunchKernelGGL(k_adj_reduce<false>, dim3(uint32_t(n) * batch), dim3(256), 0, st, partial, a, batch,
+                           nslots, slot_elems, mout);
         QF_CHECK(check_launch("adjoint reduce"));
     }
     return QF_OK;

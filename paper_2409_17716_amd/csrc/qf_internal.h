@@ -106,6 +106,7 @@ qf_status launch_diag_observable(const StateView& psi, void* lam_amps, const std
 struct AdjRows {
     uint64_t off;
     uint32_t rows, D, slot;
+    uint32_t chunk;  // rows added by one workgroup of a first launch; rows: there is none
     size_t values(uint32_t batch) const { return size_t(rows) * D * D * batch; }
 };
 // Size of the buffer that collects several gates' partial sums (needs: the values of
@@ -119,13 +120,14 @@ inline size_t collect_size(const std::vector<size_t>& needs, size_t limit) {
     }
     return std::max(most, std::min(sum, limit));
 }
-AdjRows adj_axis_rows(const StateView& s, int q);  // rows and D
+AdjRows adj_axis_rows(const StateView& s, int q);  // rows, D and chunk
 // W: the run's inverse; shift: a shift merged into the run, undone first; partial:
 // the run's rows.
 qf_status launch_adj_axis(const StateView& s, void* lam, int q, const double* W, double* partial, hipStream_t st,
                           const ShiftArg* shift);
 // mout[(b * nslots + slot) * slot_elems]: M of every listed run (complex D x D).
-qf_status launch_adj_reduce(const double* partial, const std::vector<AdjRows>& runs, uint32_t batch, double* mout,
+// Overwrites partial.
+qf_status launch_adj_reduce(double* partial, const std::vector<AdjRows>& runs, uint32_t batch, double* mout,
                             uint32_t nslots, uint32_t slot_elems, hipStream_t st);
 
 // ---- controlled rotation (k_crot.hip) ----
