@@ -918,7 +918,7 @@ qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_
                 // Up to 12 levels the shift costs no sweep of its own (layers on 12^5
                 // 164 -> 124 us); above, D computed addresses do not fit the
                 // registers beside the fibre (16^5: 455 us) and it is one (218 us).
-                if constexpr (D <= 12) {
+                if constexpr (D <= kMaxFoldedShift) {
                     if (shift) {
                         OpMatShift<T, D> op;
                         fill(op);

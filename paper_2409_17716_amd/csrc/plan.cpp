@@ -2061,14 +2061,23 @@ qf_status qf_plan_create_dims(const int32_t* dims, int32_t n, int32_t dtype, con
     return create_plan(std::vector<int>(dims, dims + n), dtype, ops, nops, nparams, opts, out);
 }
 
+// Sweeps of a per-gate schedule: a shift merged into a run of a qudit of more than
+// kMaxFoldedShift levels still takes one of its own where launch_apply_1q runs it.
+static int32_t num_sweeps(const qf_plan* p, bool adjoint) {
+    int32_t n = int32_t(p->steps.size());
+    for (const Step& s : p->steps)
+        if (s.shift_gate >= 0 && p->dims[s.q] > kMaxFoldedShift && !(adjoint && s.has_param)) ++n;
+    return n;
+}
+
 int32_t qf_plan_num_stages(const qf_plan* plan) {
     if (!plan) return -1;
-    return !staged(plan) ? int32_t(plan->steps.size()) : int32_t(plan->fwd.passes.size());
+    return !staged(plan) ? num_sweeps(plan, false) : int32_t(plan->fwd.passes.size());
 }
 
 int32_t qf_plan_num_adjoint_stages(const qf_plan* plan) {
     if (!plan) return -1;
-    return !staged(plan) ? int32_t(plan->steps.size()) : int32_t(plan->rev.passes.size());
+    return !staged(plan) ? num_sweeps(plan, true) : int32_t(plan->rev.passes.size());
 }
 
 qf_status qf_plan_forward(qf_plan* plan, const qf_state* s, const double* theta, void* stream) {

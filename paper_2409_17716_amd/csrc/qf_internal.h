@@ -65,7 +65,8 @@ inline uint32_t span(const StateView& s, int q0, int k) {
 qf_status launch_init(const StateView& s, const std::vector<uint32_t>& index, hipStream_t st);
 ShiftArg shift_arg(const StateView& s, int ctrl, int tgt, const int32_t* shift);
 // shift: a controlled shift of the same qudit in the same sweep, after U, or
-// (undo) its inverse before U.
+// (undo) its inverse before U; above kMaxFoldedShift levels in a sweep of its own.
+constexpr int kMaxFoldedShift = 12;
 qf_status launch_apply_1q(const StateView& s, int q, const double* U, hipStream_t st, const ShiftArg* shift = nullptr,
                           bool undo = false);
 qf_status launch_ctrl(const StateView& s, int ctrl, int tgt, const int32_t* shift, hipStream_t st);
