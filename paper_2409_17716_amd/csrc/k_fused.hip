@@ -189,16 +189,19 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // (mid lo, lo mid).  Relative error against 64 bits (rms; FP32 matrix cores, then
 // these), Haar blocks on Gaussian states: K = 32 1.5e-7, 4.8e-8; K = 49 1.8e-7,
 // 5.6e-8; K = 128 2.9e-7, 8.1e-8; K = 100 real 1.8e-7, 6.0e-8; diagonal phases 3.1e-8,
-// 2.6e-8; real diagonals 2.5e-8, 2.5e-8; permutations exact.  Both factors are multiplied by 2^23 first,
-// so that the parts of the smallest subnormal are normal bf16 values (the matrix core
-// takes subnormal ones for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none), and
-// the results by 2^-46.  Entries of 2^25 and more and amplitudes of 2^48 and more, whose
-// scaled sums could overflow, infinities and NaN: from a tile that holds one on (all
-// tiles, where the block does), a workgroup writes nothing in the loop and takes
-// FP32 products of the amplitudes themselves after it (plain_tile); the checks cost
-// nothing.  HBM-bound up to K = 49; time of a pass against
-// the FP32 cores: K = 36 on 6^8 26 -> 22 us, K = 49 on 7^9 317 -> 190 us, K = 100 on
-// 10^7 158 -> 87 us (real 125 -> 62), K = 128 on 2^24 280 -> 114 us.
+// 2.6e-8; real diagonals 2.5e-8, 2.5e-8; permutations exact.
+//
+// Both factors are multiplied by 2^23 first and the results by 2^-46, so that the parts
+// of the smallest subnormal are normal bf16 values (the matrix core takes subnormal ones
+// for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none).  Entries of 2^25 and more
+// and amplitudes of 2^48 and more, whose scaled sums could overflow, infinities and NaN:
+// from a tile that holds one on (all tiles, where the block does), a workgroup writes
+// nothing in the loop and takes FP32 products of the amplitudes themselves after it
+// (plain_tile); the checks cost nothing.
+//
+// HBM-bound up to K = 49; time of a pass against the FP32 cores: K = 36 on 6^8 26 -> 22
+// us, K = 49 on 7^9 317 -> 190 us (3.4 TB/s), K = 100 on 10^7 158 -> 87 us (real 125 ->
+// 62), K = 128 on 2^24 280 -> 114 us.
 //
 // A persistent workgroup of NRB wavefronts owns one row block of 16 per wavefront,
 // its block's operands in registers.  A tile of NF fibres lies in LDS as
@@ -297,8 +300,8 @@ constexpr unsigned split_waves() {
 }
 
 template <int NRB, bool REAL>
-__global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_waves<NRB>()))) void k_fused_split(cplx<float>* __restrict__ psi,
-                                                          const cplx<float>* __restrict__ B, FusedGeom g) {
+__global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_waves<NRB>()))) void k_fused_split(
+    cplx<float>* __restrict__ psi, const cplx<float>* __restrict__ B, FusedGeom g) {
     constexpr int KB = (NRB + 1) / 2;        // k blocks of 32
     constexpr int Kp = 32 * KB;
     constexpr int NF = split_fibres<NRB>();
@@ -507,7 +510,7 @@ qf_status launch_fused(const StateView& s, int k, int q0, const void* B, hipStre
             case 8: return launch_split<8>(s, g, B, real, st);
         }
     }
-    if (s.dtype == QF_C64 && K >= 32 && K <= 256) {
+    if (s.dtype == QF_C64 && K > 128 && K <= 256) {
         const uint32_t Kp = (K + 15) / 16 * 16;
         const size_t lds = size_t(2) * Kp * RS * sizeof(float);
         const uint32_t grid = (g.nfib + NTM - 1) / NTM;

@@ -1085,7 +1085,8 @@ struct MArgs {
     uint32_t blk = 0;
 };
 
-// One round on the tiles t[0 .. NT) (the adjoint runs psi and lam together).
+// One round on the tiles t[0 .. NT) (the complex128 adjoint runs psi and lam together;
+// the complex64 adjoint takes run_round2).
 // The common round shapes (one U on position 0 or 1, two U on positions 0 and
 // 1, one PHASE, permutations only) run straight from the LDS loads to the LDS stores
 // (no op dispatch while the sub-tile is live in registers, so no register
@@ -1095,15 +1096,13 @@ __device__ __forceinline__ void run_round(cplx<T>* const (&t)[NT], const StageGe
                                           uint32_t base, const RoundDesc& rd, const StageOp* __restrict__ ops,
                                           const cplx<T>* __restrict__ mats, const SubDigits& dig0,
                                           const MArgs& ma = MArgs{}) {
+    static_assert(NT == 1 || sizeof(T) == 8, "two complex64 tiles are interleaved (run_round2)");
     constexpr int DM = cpow(D, M);
     constexpr uint32_t ESZ = uint32_t(sizeof(cplx<T>));
     MAcc<T, D> macc;
     if constexpr (MACC) {
 #pragma unroll
-        for (int e = 0; e < D * D; ++e) {
-            macc.re[e] = T(0);
-            if constexpr (!MAcc<T, D>::kAnti) macc.im[e] = T(0);
-        }
+        for (int e = 0; e < D * D; ++e) macc.re[e] = T(0);
     }
     const uint32_t nsub = g.TE / DM;
     // LDS byte addresses: tile 0's base goes into each sub-tile base; the
