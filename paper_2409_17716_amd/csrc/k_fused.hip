@@ -193,15 +193,17 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 //
 // Both factors are multiplied by 2^23 first and the results by 2^-46, so that the parts
 // of the smallest subnormal are normal bf16 values (the matrix core takes subnormal ones
-// for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none).  Entries of 2^25 and more
-// and amplitudes of 2^48 and more, whose scaled sums could overflow, infinities and NaN:
-// from a tile that holds one on (all tiles, where the block does), a workgroup writes
-// nothing in the loop and takes FP32 products of the amplitudes themselves after it
-// (plain_tile); the checks cost nothing.
+// for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none).  Rows whose entries add up
+// to 2^25 and more and amplitudes of 2^55 and more, whose scaled sums could overflow,
+// infinities and NaN: from a tile that holds one on (all tiles, where a row of the block
+// does), a workgroup writes nothing in the loop and takes FP32 products of the
+// amplitudes themselves after it (plain_tile); the checks cost nothing.
 //
-// HBM-bound up to K = 49; time of a pass against the FP32 cores: K = 36 on 6^8 26 -> 22
-// us, K = 49 on 7^9 317 -> 190 us (3.4 TB/s), K = 100 on 10^7 158 -> 87 us (real 125 ->
-// 62), K = 128 on 2^24 280 -> 114 us.
+// HBM-bound up to K = 49; time of a pass against the FP32 cores: K = 36 on 6^8 26 -> 20
+// us, K = 49 on 7^9 317 -> 181 us (3.6 TB/s), K = 100 on 10^7 158 -> 88 us (real 125 ->
+// 62), K = 128 on 2^24 280 -> 114 us.  One tile (K = 100 on 10^4) waits for the block's
+// operands: 19.7 us with a check and two selections per entry, 18.7 with the row sums
+// (FP32 cores 18.9).
 //
 // A persistent workgroup of NRB wavefronts owns one row block of 16 per wavefront,
 // its block's operands in registers.  A tile of NF fibres lies in LDS as
@@ -232,10 +234,12 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
     }
 }
 
-// Scale of the factors, and log2 of the scaled amplitudes' and entries' limits: 128
-// products of each kind add up to less than 2^(7 + 71 + 48 + 1).
+// Scale of the factors, and the limits of a row's sum and (log2) of an amplitude's part,
+// both scaled: each of the sums of products stays below 2^(48 + 78), their difference
+// below 2^127.
 constexpr float kSplitScale = 0x1p23f, kSplitBack = 0x1p-46f;
-constexpr int kSplitX = 48 + 23, kSplitB = 25 + 23;
+constexpr float kSplitB = 0x1p48f;
+constexpr int kSplitX = 78;
 
 // Any of the eight leading parts at or above 2^E, infinite or NaN.
 template <int E>
@@ -321,34 +325,33 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
     if (threadIdx.x == 0) plain = ~0u;
     // the block's rows 16 wave + lr: parts of the real and imaginary entries
     u32x4 br[KB][3], bi[REAL ? 1 : KB][3];
-    bool over = false;
-    float largest = 0.f, sum = 0.f;  // of the row's entries
+    float largest = 0.f, sum = 0.f;  // |re| + |im| of the row's entries
     {
         const uint32_t row = uint32_t(16 * wave + lr);
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            // unconditional loads (of a clamped address) stay together: K = 121 on 11^6
-            // 32 us with them under their conditions, 25 us so
+            // unconditional loads stay together (K = 121 on 11^6 32 us with them under
+            // their conditions, 25 us so): the last k block's past the row read its last entry
             cplx<float> u[8];
+            float sc[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                u[i] = B[min(row, g.K - 1) * g.K + min(uint32_t(32 * kb + 8 * lk + i), g.K - 1)];
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t col = uint32_t(32 * kb + 8 * lk + i);
+                const bool in = row < g.K && (kb + 1 < KB || col < g.K);
+                u[i] = B[min(row, g.K - 1) * g.K + (kb + 1 < KB ? col : min(col, g.K - 1))];
+                sc[i] = in ? kSplitScale : 0.f;
+            }
             float xr[8], xi[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const bool in = row < g.K && uint32_t(32 * kb + 8 * lk + i) < g.K;
-                xr[i] = in ? u[i].re * kSplitScale : 0.f;
-                xi[i] = in ? u[i].im * kSplitScale : 0.f;
+                xr[i] = u[i].re * sc[i];
+                xi[i] = u[i].im * sc[i];
                 const float m = fabsf(xr[i]) + fabsf(xi[i]);
                 largest = fmaxf(largest, m);
                 sum += m;
             }
             split8(xr, br[kb]);
-            over |= split_over<kSplitB>(br[kb][0]);
-            if constexpr (!REAL) {
-                split8(xi, bi[kb]);
-                over |= split_over<kSplitB>(bi[kb][0]);
-            }
+            if constexpr (!REAL) split8(xi, bi[kb]);
         }
     }
 #pragma unroll
@@ -357,6 +360,7 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
         sum += __shfl_xor(sum, m, 64);
     }
     const bool dominated = __any(largest > 0.f && sum <= 2.5f * largest);
+    bool over = !(sum < kSplitB);  // or NaN
     const uint32_t ntiles = (g.nfib + NF - 1) / NF;
     cplx<float> x[UPL][8];
     // unit u: fibre u % NF, rows 8 (u / NF) .. + 7 (consecutive lanes: consecutive

@@ -60,7 +60,7 @@ def test_block_entries_without_parts(dims, span, q0):
 
 @pytest.mark.parametrize("dims,span,q0", SHAPES)
 @pytest.mark.parametrize("ex,eb", [(-100, 0), (-117, 0), (-122, 0), (-60, -60), (0, -117), (20, 20), (47, 0),
-                                   (50, 0), (0, 26)])
+                                   (50, 0), (57, 0), (0, 20), (0, 26)])
 def test_scales(dims, span, q0, ex, eb):
     """Amplitudes about 2^ex and a block of 2^eb times a unitary: results keep FP32's
     relative precision as long as they are normal numbers themselves (each of the fibre's
