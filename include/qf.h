@@ -159,8 +159,11 @@ qf_status qf_apply_mcx(const qf_state* s, int32_t nctrl, const int32_t* ctrls, i
  * with the register viewed as [D^q0][D^k][D^(n-q0-k)] (mixed: K = d_q0 ... d_{q0+k-1}
  * in place of D^k).
  * B: DEVICE pointer, D^k x D^k row-major in the state's precision (complex64
- * or complex128), caller-owned, read during the kernel.  complex64 blocks with
- * D^k >= 32 run on FP32 matrix cores; others on vector ALUs.  D^k <= 1024. */
+ * or complex128), caller-owned, read during the kernel.  complex64 blocks of
+ * 32 <= D^k <= 128 run on the bf16 matrix cores with every FP32 operand as three
+ * bf16 parts (no further from exact than FP32 products; rows whose entries add up
+ * to 2^25 and amplitudes from 2^55 take FP32 products), up to 256 on the FP32
+ * matrix cores; others on vector ALUs.  D^k <= 1024. */
 qf_status qf_apply_fused(const qf_state* s, int32_t k, int32_t q0, const void* B,
                          void* stream);
 

@@ -295,7 +295,8 @@ uint32_t crot_rows(const StateView& s, int tgt) { return (s.N / s.dims[tgt] + kC
 qf_status launch_crot(const StateView& s, const CrotArgs& a, const void* dtab, size_t tab_stride, const double* htab,
                       hipStream_t st) {
     const CrGeom g = make_geom(s, a);
-    // 64 workgroups of four fibres per lane left a 4^9 register's launch at 4.8 us
+    // by workgroups at four fibres per lane: 64 3.2 us so, 2.5 with one per lane; 256 3.9, 3.4;
+    // 512 4.9, 4.6; 1024 7.6, 7.1; 2048 10.5, 11.0 (complex64 qubits)
     const bool one = uint64_t(g.bprf) * s.batch < 512;
     return with_dim_c(s.dims[a.tgt], [&](auto dtag) -> qf_status {
         constexpr int D = decltype(dtag)::value;
