@@ -201,9 +201,8 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 //
 // HBM-bound up to K = 49; time of a pass against the FP32 cores: K = 36 on 6^8 26 -> 20
 // us, K = 49 on 7^9 317 -> 181 us (3.6 TB/s), K = 100 on 10^7 158 -> 88 us (real 125 ->
-// 62), K = 128 on 2^24 280 -> 114 us.  One tile (K = 100 on 10^4) waits for the block's
-// operands: 19.7 us with a check and two selections per entry, 18.7 with the row sums
-// (FP32 cores 18.9).
+// 62), K = 128 on 2^24 280 -> 114 us.  Small registers: K = 100 on 10^5
+// 18.4 -> 12 us, K = 49 on 7^5 12.7 -> 11, K = 128 on 2^15 22 -> 15.5.
 //
 // A persistent workgroup of NRB wavefronts owns one row block of 16 per wavefront,
 // its block's operands in registers.  A tile of NF fibres lies in LDS as
@@ -255,7 +254,8 @@ __device__ __forceinline__ bool split_over(const u32x4& hi) {
 
 // Fibres per tile: 64 (512-byte runs of HBM), 32 for K <= 48, where more and
 // smaller workgroups do better (K = 32 on 2^24 amplitudes 54 against 70 us; K = 100
-// on 10^7 108 against 85 us).
+// on 10^7 108 against 85 us); 16 where the register's fibres then make at most one
+// workgroup a CU (launch_split).
 template <int NRB>
 constexpr int split_fibres() {
     return NRB <= 3 ? 32 : 64;
@@ -300,15 +300,14 @@ __device__ __forceinline__ void plain_tile(cplx<float>* __restrict__ psi, const 
 // 25 us with 2 of them, 22 with 3), other sizes what the compiler finds.
 template <int NRB>
 constexpr unsigned split_waves() {
-    return NRB == 3 || NRB == 4 ? 3 : (NRB + 3) / 4;
+    return NRB == 3 || NRB == 4 ? 3 : 1;
 }
 
-template <int NRB, bool REAL>
+template <int NRB, int NF, bool REAL>
 __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_waves<NRB>()))) void k_fused_split(
     cplx<float>* __restrict__ psi, const cplx<float>* __restrict__ B, FusedGeom g) {
     constexpr int KB = (NRB + 1) / 2;        // k blocks of 32
     constexpr int Kp = 32 * KB;
-    constexpr int NF = split_fibres<NRB>();
     constexpr int CS = Kp * 2 + 16;          // bytes between fibres of a plane
     constexpr int PL = NF * CS;              // bytes of a plane
     constexpr int NT = 64 * NRB;
@@ -471,10 +470,9 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
 }
 
 // The grid fills the LDS of 256 CUs once.
-template <int NRB>
+template <int NRB, int NF>
 qf_status launch_split(const StateView& s, const FusedGeom& g, const void* B, bool real, hipStream_t st) {
     constexpr int Kp = 32 * ((NRB + 1) / 2);
-    constexpr uint32_t NF = split_fibres<NRB>();
     constexpr size_t lds = size_t(6) * NF * (Kp * 2 + 16);
     constexpr uint32_t cap = 256 * std::max<uint32_t>(1, uint32_t(160 * 1024 / lds));
     const uint32_t ntiles = (g.nfib + NF - 1) / NF;
@@ -482,10 +480,19 @@ qf_status launch_split(const StateView& s, const FusedGeom& g, const void* B, bo
     auto* amps = reinterpret_cast<cplx<float>*>(s.amps);
     auto* mat = reinterpret_cast<const cplx<float>*>(B);
     if (real)
-        hipLaunchKernelGGL((k_fused_split<NRB, true>), dim3(grid), dim3(64 * NRB), lds, st, amps, mat, g);
+        hipLaunchKernelGGL((k_fused_split<NRB, NF, true>), dim3(grid), dim3(64 * NRB), lds, st, amps, mat, g);
     else
-        hipLaunchKernelGGL((k_fused_split<NRB, false>), dim3(grid), dim3(64 * NRB), lds, st, amps, mat, g);
+        hipLaunchKernelGGL((k_fused_split<NRB, NF, false>), dim3(grid), dim3(64 * NRB), lds, st, amps, mat, g);
     return check_launch("qf_apply_fused (bf16 matrix cores)");
+}
+
+// Up to 4096 fibres (a workgroup a CU) the pass waits for one tile's chain of loads, split
+// and products, which is shorter for 16 fibres than for 64 on a few CUs (K = 100 on
+// 10^5 19.4 -> 12 us, K = 128 on 2^15 21.7 -> 15.5, K = 36 on 6^7 12 -> 11).
+template <int NRB>
+qf_status launch_split(const StateView& s, const FusedGeom& g, const void* B, bool real, hipStream_t st) {
+    return g.nfib <= 16 * 256 ? launch_split<NRB, 16>(s, g, B, real, st)
+                              : launch_split<NRB, split_fibres<NRB>()>(s, g, B, real, st);
 }
 
 }  // namespace
