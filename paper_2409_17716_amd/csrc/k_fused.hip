@@ -191,13 +191,13 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // 5.6e-8; K = 128 2.9e-7, 8.1e-8; K = 100 real 1.8e-7, 6.0e-8; diagonal phases 3.1e-8,
 // 2.6e-8; real diagonals 2.5e-8, 2.5e-8; permutations exact.
 //
-// Both factors are multiplied by 2^23 first and the results by 2^-46, so that the parts
-// of the smallest subnormal are normal bf16 values (the matrix core takes subnormal ones
-// for zero: amplitudes of 1e-36 kept 8 bits, of 1e-39 none).  Rows whose entries add up
-// to 2^25 and more and amplitudes of 2^55 and more, whose scaled sums could overflow,
-// infinities and NaN: from a tile that holds one on (all tiles, where a row of the block
-// does), a workgroup writes nothing in the loop and takes FP32 products of the
-// amplitudes themselves after it (plain_tile); the checks cost nothing.
+// The amplitudes are multiplied by 2^23 and a row of the block by the power of two that
+// brings its sum to 2^47 to 2^48, the results by their inverse, so that the parts of the
+// smallest numbers are normal bf16 values (the matrix core takes subnormal ones for
+// zero: unscaled, amplitudes of 1e-36 kept 8 bits, of 1e-39 none).  Amplitudes of 2^55
+// and more, whose sums could overflow, infinities and NaN: from a tile that holds one on
+// (all tiles, where a row's sum is infinite or NaN), a workgroup writes nothing in the
+// loop and takes FP32 products of the amplitudes themselves after it (plain_tile).
 //
 // HBM-bound up to K = 49; time of a pass against the FP32 cores: K = 36 on 6^8 26 -> 20
 // us, K = 49 on 7^9 317 -> 181 us (3.6 TB/s), K = 100 on 10^7 158 -> 88 us (real 125 ->
@@ -233,11 +233,9 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
     }
 }
 
-// Scale of the factors, and the limits of a row's sum and (log2) of an amplitude's part,
-// both scaled: each of the sums of products stays below 2^(48 + 78), their difference
-// below 2^127.
-constexpr float kSplitScale = 0x1p23f, kSplitBack = 0x1p-46f;
-constexpr float kSplitB = 0x1p48f;
+// Scale of the amplitudes, and log2 of the limit of their scaled parts: with rows of
+// sums below 2^48 each sum of products stays below 2^126, a difference below 2^127.
+constexpr float kSplitScale = 0x1p23f, kSplitBack = 0x1p-23f;
 constexpr int kSplitX = 78;
 
 // Any of the eight leading parts at or above 2^E, infinite or NaN.
@@ -324,42 +322,56 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
     if (threadIdx.x == 0) plain = ~0u;
     // the block's rows 16 wave + lr: parts of the real and imaginary entries
     u32x4 br[KB][3], bi[REAL ? 1 : KB][3];
-    float largest = 0.f, sum = 0.f;  // |re| + |im| of the row's entries
+    // scales of result rows 4 i .. 4 i + 3, in the fibres' padding from plane 1 on
+    auto back_of = [&](int i) { return reinterpret_cast<f32x4*>(smem + (1 + i / NF) * PL + i % NF * CS + Kp * 2); };
+    bool dominated, over;
     {
         const uint32_t row = uint32_t(16 * wave + lr);
+        // unconditional loads stay together (K = 121 on 11^6 32 us with them under their
+        // conditions, 25 us so): the last k block's past the row read its last entry
+        cplx<float> u[KB][8];
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            // unconditional loads stay together (K = 121 on 11^6 32 us with them under
-            // their conditions, 25 us so): the last k block's past the row read its last entry
-            cplx<float> u[8];
-            float sc[8];
+        for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const uint32_t col = uint32_t(32 * kb + 8 * lk + i);
-                const bool in = row < g.K && (kb + 1 < KB || col < g.K);
-                u[i] = B[min(row, g.K - 1) * g.K + (kb + 1 < KB ? col : min(col, g.K - 1))];
-                sc[i] = in ? kSplitScale : 0.f;
+                u[kb][i] = B[min(row, g.K - 1) * g.K + (kb + 1 < KB ? col : min(col, g.K - 1))];
             }
+        float largest = 0.f, sum = 0.f;  // |re| + |im| of the row's entries
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const bool in = kb + 1 < KB || uint32_t(32 * kb + 8 * lk + i) < g.K;
+                const float m = fabsf(u[kb][i].re) + fabsf(u[kb][i].im);
+                largest = fmaxf(largest, m);
+                sum += in ? m : 0.f;
+            }
+#pragma unroll
+        for (int m = 16; m < 64; m <<= 1) {
+            largest = fmaxf(largest, __shfl_xor(largest, m, 64));
+            sum += __shfl_xor(sum, m, 64);
+        }
+        over = !(sum < __builtin_inff());  // or NaN
+        dominated = __any(row < g.K && largest > 0.f && sum <= 2.5f * largest);
+        // the row's sum becomes 2^47 to 2^48 (2^126 is the largest scale)
+        const int e = min(48 - __builtin_amdgcn_frexp_expf(sum), 126);
+        const float scale = row < g.K ? ldexpf(1.f, e) : 0.f;
+        if (lk == 0) reinterpret_cast<float*>(back_of(4 * wave + (lr >> 2)))[lr & 3] = ldexpf(kSplitBack, -e);
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
             float xr[8], xi[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                xr[i] = u[i].re * sc[i];
-                xi[i] = u[i].im * sc[i];
-                const float m = fabsf(xr[i]) + fabsf(xi[i]);
-                largest = fmaxf(largest, m);
-                sum += m;
+                const bool in = kb + 1 < KB || uint32_t(32 * kb + 8 * lk + i) < g.K;
+                const float sc = in ? scale : 0.f;
+                xr[i] = u[kb][i].re * sc;
+                xi[i] = u[kb][i].im * sc;
             }
             split8(xr, br[kb]);
             if constexpr (!REAL) split8(xi, bi[kb]);
         }
     }
-#pragma unroll
-    for (int m = 16; m < 64; m <<= 1) {
-        largest = fmaxf(largest, __shfl_xor(largest, m, 64));
-        sum += __shfl_xor(sum, m, 64);
-    }
-    const bool dominated = __any(largest > 0.f && sum <= 2.5f * largest);
-    bool over = !(sum < kSplitB);  // or NaN
     const uint32_t ntiles = (g.nfib + NF - 1) / NF;
     cplx<float> x[UPL][8];
     // unit u: fibre u % NF, rows 8 (u / NF) .. + 7 (consecutive lanes: consecutive
@@ -457,10 +469,11 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
             const uint32_t f = tile * NF + uint32_t(16 * j + lr);
             if (f < g.nfib && tile < stop) {
                 const uint32_t base = fibre_base(g, f);
+                const f32x4 back = *back_of(4 * wave + lk);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const uint32_t row = uint32_t(16 * wave + 4 * lk + r);
-                    if (row < g.K) psi[base + row * g.L] = cmake<float>(rr[0][r] * kSplitBack, ri[0][r] * kSplitBack);
+                    if (row < g.K) psi[base + row * g.L] = cmake<float>(rr[0][r] * back[r], ri[0][r] * back[r]);
                 }
             }
         }

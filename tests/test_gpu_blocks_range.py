@@ -77,6 +77,21 @@ def test_scales(dims, span, q0, ex, eb):
     assert err <= np.sqrt(2 * K / 3) * 2.0 ** -24, (err, ex, eb)
 
 
+@pytest.mark.parametrize("dims,span,q0", SHAPES)
+@pytest.mark.parametrize("decades", [8, 30, 60])
+def test_rows_of_different_sizes(dims, span, q0, decades):
+    """Rows of a block over many powers of two, smallest and largest side by side: every
+    row keeps FP32's relative precision (test_scales' bound)."""
+    H, K, L = _split(dims, span, q0)
+    rng = np.random.default_rng(45)
+    x = (rng.standard_normal((H, K, L)) + 1j * rng.standard_normal((H, K, L))).astype(np.complex64)
+    U = (qi.random_unitary(K, rng) * 10.0 ** rng.uniform(-decades / 2, decades / 2, size=(K, 1))).astype(np.complex64)
+    got = _apply(dims, span, q0, U, x)
+    wr, wi = _parts(U.astype(np.complex128), x, False)
+    err = np.sqrt(((got.real - wr) ** 2 + (got.imag - wi) ** 2).mean(axis=(0, 2)) / (wr ** 2 + wi ** 2).mean(axis=(0, 2)))
+    assert np.all(err <= np.sqrt(2 * K / 3) * 2.0 ** -24), (err.max(), K)
+
+
 def _fp32(U, x):
     """U x for one entry per row, each part by FP32 products and one FP32 addition."""
     K = U.shape[0]
