@@ -195,9 +195,10 @@ __global__ __launch_bounds__(kBlock) void k_fused_mfma(cplx<float>* __restrict__
 // brings its sum to 2^47 to 2^48, the results by their inverse, so that the parts of the
 // smallest numbers are normal bf16 values (the matrix core takes subnormal ones for
 // zero: unscaled, amplitudes of 1e-36 kept 8 bits, of 1e-39 none).  Amplitudes of 2^55
-// and more, whose sums could overflow, infinities and NaN: from a tile that holds one on
-// (all tiles, where a row's sum is infinite or NaN), a workgroup writes nothing in the
-// loop and takes FP32 products of the amplitudes themselves after it (plain_tile).
+// and more, whose sums could overflow, and infinities: from a tile that holds one on (all
+// tiles, where a row's sum is infinite or NaN), a workgroup writes nothing in the loop
+// and takes FP32 products of the amplitudes themselves after it (plain_tile).  A NaN's
+// parts are NaN, and so are its products, as in FP32.
 //
 // HBM-bound up to K = 49; time of a pass against the FP32 cores: K = 36 on 6^8 26 -> 20
 // us, K = 49 on 7^9 317 -> 181 us (3.6 TB/s), K = 100 on 10^7 158 -> 88 us (real 125 ->
@@ -233,22 +234,10 @@ __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
     }
 }
 
-// Scale of the amplitudes, and log2 of the limit of their scaled parts: with rows of
-// sums below 2^48 each sum of products stays below 2^126, a difference below 2^127.
+// Scale of the amplitudes, and the limit of their scaled parts: with rows of sums below
+// 2^48 each sum of products stays below 2^126, a difference below 2^127.
 constexpr float kSplitScale = 0x1p23f, kSplitBack = 0x1p-23f;
-constexpr int kSplitX = 78;
-
-// Any of the eight leading parts at or above 2^E, infinite or NaN.
-template <int E>
-__device__ __forceinline__ bool split_over(const u32x4& hi) {
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-    u16x2 m = {0, 0};
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-        m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, uint32_t(hi[i] & 0x7fff7fffu)));
-    constexpr uint16_t lim = uint16_t((E + 127) << 7);
-    return m.x >= lim || m.y >= lim;
-}
+constexpr float kSplitX = 0x1p78f;
 
 // Fibres per tile: 64 (512-byte runs of HBM), 32 for K <= 48, where more and
 // smaller workgroups do better (K = 32 on 2^24 amplitudes 54 against 70 us; K = 100
@@ -400,6 +389,7 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
     if (tile < ntiles) fetch(tile);
     for (; tile < ntiles; tile += gridDim.x) {
         __syncthreads();  // the previous tile's operands are read
+        float top = 0.f;  // largest part of this lane's amplitudes
 #pragma unroll
         for (int t = 0; t < UPL; ++t) {
             uint32_t f, k8;
@@ -412,15 +402,17 @@ __global__ __launch_bounds__(64 * NRB) __attribute__((amdgpu_waves_per_eu(split_
             split8(v, part);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + q * PL) = part[q];
-            over |= split_over<kSplitX>(part[0]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = x[t][i].im * kSplitScale;
+            for (int i = 0; i < 8; ++i) {
+                top = fmaxf(top, fabsf(v[i]));
+                v[i] = x[t][i].im * kSplitScale;
+                top = fmaxf(top, fabsf(v[i]));
+            }
             split8(v, part);
-            over |= split_over<kSplitX>(part[0]);
 #pragma unroll
             for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(p + (3 + q) * PL) = part[q];
         }
-        if (over) atomicMin(&plain, tile);
+        if (over || top >= kSplitX) atomicMin(&plain, tile);
         __syncthreads();
         const uint32_t stop = plain;
         if (tile + gridDim.x < ntiles) fetch(tile + gridDim.x);
