@@ -161,7 +161,7 @@ qf_status qf_apply_mcx(const qf_state* s, int32_t nctrl, const int32_t* ctrls, i
  * B: DEVICE pointer, D^k x D^k row-major in the state's precision (complex64
  * or complex128), caller-owned, read during the kernel.  complex64 blocks of
  * 32 <= D^k <= 128 run on the bf16 matrix cores with every FP32 operand as three
- * bf16 parts (no further from exact than FP32 products; amplitudes from 2^55 and
+ * bf16 parts (FP32 precision at every scale; amplitudes from 2^55 and
  * infinities take FP32 products), up to 256 on the FP32 matrix cores;
  * others on vector ALUs.  D^k <= 1024. */
 qf_status qf_apply_fused(const qf_state* s, int32_t k, int32_t q0, const void* B,
